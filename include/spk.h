@@ -98,7 +98,11 @@ typedef enum {
                                  The stop test stays on the unpreconditioned residual ||r|| */
 } spk_precond;
 typedef enum {
-    SPK_EXEC_AUTO = 0,        /* the library's choice: the host loop, which measured fastest */
+    SPK_EXEC_AUTO = 0,        /* the library's choice: CG without a preconditioner on a small system
+                                 (one row per thread of one 512-thread workgroup per CU, rows of at
+                                 most 32 entries) as one launch that holds the matrix on the chip,
+                                 or, when the device is too busy to run that launch's workgroups
+                                 together, and for every other solve, the host loop */
     SPK_EXEC_HOST_LOOP = 1,   /* kernels launched from a host loop, status polled per chunk */
     SPK_EXEC_GRAPH = 2,       /* chunks of iterations replayed from a captured HIP graph */
     SPK_EXEC_PERSISTENT = 3   /* FP64 CG: the whole solve in one cooperative launch with grid
@@ -290,8 +294,8 @@ spk_status spk_free(spk_plan plan);
  * HOST_LOOP execution and no history.  A: square, F64 values, at most
  * spk_noalloc_max_rows() rows (the scratch holds the solve state, the
  * reduction partials and the vectors of n doubles: r, p, q, and their second
- * buffers when the solve runs one launch per iteration, as systems of up to
- * 2^20 rows do); the caller's arrays
+ * buffers when the solve runs one launch per iteration, or the exchange
+ * buffers of one that runs as a single launch); the caller's arrays
  * are borrowed for the call only.  b and x as for spk_execute_solve.  The
  * launch shape is one an earlier plan of the same shape tuned on this
  * context (never tuned here), else the heuristic one, so a solve after such

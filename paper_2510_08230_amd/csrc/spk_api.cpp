@@ -58,7 +58,7 @@ struct spk_ctx_s {
     int wall_khz = 0;                   // wall_clock64() rate
     std::string err;
     unsigned *d_flags = nullptr;
-    unsigned *h_flags = nullptr;        // pinned; [2], [3]: the pattern probe's words
+    unsigned *h_flags = nullptr;        // pinned; [0..2] the validation's words, [3], [4] the pattern probe's
     long long *d_probe = nullptr;       // pattern probe: offset table (kCodeSlots) and 4 words
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t ev_snap = nullptr;       // marks a state snapshot copy in the solve loops
@@ -84,6 +84,11 @@ struct spk_plan_s {
     unsigned *bar = nullptr;             // persistent grid-barrier words
     spk::PersistResult *persist_res = nullptr;   // persistent mixed solve: its result (device)
     spk_plan_info info{};
+    // resident solve (one launch, the matrix on the chip; res_grid = 0: not used)
+    int res_grid = 0, res_rows = 0, res_lds = 0;
+    unsigned res_epoch = 0;              // launches made on res_ctl
+    unsigned *res_ctl = nullptr;         // control words, then the grid-sum slots
+    void *res_xch = nullptr;             // exchange buffers
     double *r = nullptr, *p = nullptr, *q = nullptr, *partials = nullptr, *hist = nullptr;
     int algo = 0;                        // ALGO_CG / ALGO_CGS / ALGO_PCG
     double *rt = nullptr, *u = nullptr, *v = nullptr, *uh = nullptr;   // CGS
@@ -173,19 +178,23 @@ CsrDev to_dev(const spk_csr *A) {
 
 size_t vec_bytes(int val_t) { return val_t == SPK_F64 ? 8 : 4; }
 
-// max_row (optional): the longest row's entry count (valid for a valid A).
-spk_status gpu_verdict(spk_ctx ctx, const spk_csr *A, int32_t *verdict, int64_t *max_row = nullptr) {
+// max_row (optional): the longest row's entry count; with chunk > 0,
+// max_chunk: the most entries in chunk consecutive rows (row 0, chunk, ... on);
+// both valid for a valid A.
+spk_status gpu_verdict(spk_ctx ctx, const spk_csr *A, int32_t *verdict, int64_t *max_row = nullptr,
+                       int64_t chunk = 0, int64_t *max_chunk = nullptr) {
     if (A->n_rows < 0 || A->n_cols < 0 || A->nnz < 0) {
         *verdict = SPK_CSR_BAD_SIZE;
         return SPK_OK;
     }
     const CsrDev d = to_dev(A);
-    SPK_HIP(ctx, hipMemsetAsync(ctx->d_flags, 0, 2 * sizeof(unsigned), ctx->stream));
-    SPK_HIP(ctx, spk::launch_validate(d, ctx->d_flags, ctx->num_cu * 4, ctx->stream));
-    SPK_HIP(ctx, hipMemcpyAsync(ctx->h_flags, ctx->d_flags, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream));
+    SPK_HIP(ctx, hipMemsetAsync(ctx->d_flags, 0, 3 * sizeof(unsigned), ctx->stream));
+    SPK_HIP(ctx, spk::launch_validate(d, ctx->d_flags, chunk, ctx->num_cu * 4, ctx->stream));
+    SPK_HIP(ctx, hipMemcpyAsync(ctx->h_flags, ctx->d_flags, 3 * sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream));
     SPK_HIP(ctx, hipStreamSynchronize(ctx->stream));
     const unsigned f = ctx->h_flags[0];
     if (max_row) *max_row = ctx->h_flags[1];
+    if (max_chunk) *max_chunk = ctx->h_flags[2];
     int32_t v = SPK_CSR_OK;
     if (f & spk::VFLAG_BAD_FIRST) v = SPK_CSR_BAD_FIRST;
     else if (f & spk::VFLAG_DECREASING) v = SPK_CSR_DECREASING;
@@ -544,6 +553,7 @@ enum { ALGO_CG = 0, ALGO_CGS = 1, ALGO_PCG = 2, ALGO_GMRES = 3 };
 // kFusedMaxRows when the pattern is banded (pattern_regular); never above.
 // SPK_CG_FUSED=1 / 0 forces it on / off (0 also rules out the persistent
 // mode).
+constexpr int64_t kResidentMaxIters = 100000;   // bounds one launch (about half a second)
 constexpr int64_t kFusedMaxRows = int64_t(1) << 17;
 constexpr int64_t kFusedMaxRowsAny = int64_t(1) << 16;
 
@@ -569,10 +579,46 @@ spk_status pattern_regular(spk_ctx ctx, const CsrDev &A, bool *regular) {
     long long *table = ctx->d_probe;
     unsigned *words = reinterpret_cast<unsigned *>(table + spk::kCodeSlots);
     SPK_HIP(ctx, spk::launch_pattern_probe(A, 8, table, words, ctx->num_cu * 8, ctx->stream));
-    SPK_HIP(ctx, hipMemcpyAsync(ctx->h_flags + 2, words, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream));
+    SPK_HIP(ctx, hipMemcpyAsync(ctx->h_flags + 3, words, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream));
     SPK_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    *regular = ctx->h_flags[3] == 0 && ctx->h_flags[2] <= static_cast<unsigned>(spk::kCodeDict);
+    *regular = ctx->h_flags[4] == 0 && ctx->h_flags[3] <= static_cast<unsigned>(spk::kCodeDict);
     return SPK_OK;
+}
+
+// ------------------------------------------------------------------ resident solves
+// Rows per workgroup of a resident solve of n rows.  Fewer workgroups make
+// the exchange cheaper, more of them share the row work: 256 rows up to 128
+// workgroups, 512 above (us per solve with 256 / 512 rows: stencil7
+// n = 1,000: 142 / 150, n = 15,625: 196 / 196, n = 97,336: 250 / 228; random
+// pattern n = 20,011: 338 / 351, n = 100,000: 461 / 443).
+int resident_rows(int64_t n) { return n <= 32768 ? 256 : spk::kResidentRows; }
+
+// Whether a solve of this configuration may run as one resident launch (its
+// entries still have to fit, resident_fits): CG in the library's own choice of
+// execution, unless an environment switch asks for a particular loop or
+// kernel, up to one row per thread of one workgroup per CU.
+bool resident_wanted(spk_ctx ctx, const spk_solver_cfg &cfg, int64_t n) {
+    if (cfg.solver != SPK_SOLVER_CG || cfg.precond != SPK_PRECOND_NONE || cfg.exec_mode != SPK_EXEC_AUTO) return false;
+    if (std::getenv("SPK_CG_FUSED") || std::getenv("SPK_SPMV_KERNEL")) return false;
+    const char *e = std::getenv("SPK_RESIDENT");
+    if (e && std::strcmp(e, "0") == 0) return false;
+    const int64_t grid = n < 1 ? 0 : (n + resident_rows(n) - 1) / resident_rows(n);
+    return grid >= 1 && grid <= std::min(ctx->num_cu, spk::kResidentGrid) && cfg.max_iters <= kResidentMaxIters;
+}
+
+// Control words and grid-sum slots of a resident solve, in bytes.
+constexpr size_t kResidentCtlBytes = 64 + sizeof(unsigned long long) * spk::kResidentSlots;
+
+// Sets the plan's resident launch shape; false when a row is too long for one
+// thread or the workgroups' entries past the registers do not fit LDS.
+bool resident_shape(spk_plan pl, int rows, int64_t max_chunk, bool mixed) {
+    if (pl->A.max_row > spk::kResidentRowMax) return false;
+    const int64_t lds = pl->A.max_row <= spk::kResidentRegs ? 0 : max_chunk;
+    if (lds > INT32_MAX || spk::resident_lds_bytes(lds, mixed) > spk::kResidentLds) return false;
+    pl->res_rows = rows;
+    pl->res_lds = static_cast<int>(lds);
+    pl->res_grid = static_cast<int>((pl->A.n_rows + rows - 1) / rows);
+    return true;
 }
 
 // st->x := ptr (the tuner's runs of the fused step write through st->x).
@@ -790,6 +836,10 @@ void release_workspace(spk_plan pl) {
     ctx->dpool.put(pl->bar);
     ctx->dpool.put(pl->persist_res);
     pl->persist_res = nullptr;
+    ctx->dpool.put(pl->res_ctl);
+    ctx->dpool.put(pl->res_xch);
+    pl->res_ctl = nullptr;
+    pl->res_xch = nullptr;
     ctx->dpool.put(pl->rt);
     ctx->dpool.put(pl->u);
     ctx->dpool.put(pl->v);
@@ -890,8 +940,8 @@ spk_status spk_init(int device_id, void *hip_stream, spk_ctx *out) {
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) ctx->dpool.set_cap(total_b / 4);
     ctx->hpool.set_cap(size_t(16) << 20);
     if (hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipMalloc(&ctx->d_flags, 2 * sizeof(unsigned)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void **>(&ctx->h_flags), 4 * sizeof(unsigned), hipHostMallocDefault) !=
+        hipMalloc(&ctx->d_flags, 3 * sizeof(unsigned)) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->h_flags), 5 * sizeof(unsigned), hipHostMallocDefault) !=
             hipSuccess ||
         hipMalloc(&ctx->d_probe, sizeof(long long) * spk::kCodeSlots + 4 * sizeof(unsigned)) != hipSuccess ||
         hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
@@ -947,14 +997,15 @@ spk_status spk_partition(spk_ctx ctx, const spk_csr *A, int64_t parts, int64_t *
     return SPK_OK;
 }
 
-static spk_status plan_common(spk_ctx ctx, const spk_csr *A, spk_plan *out, int64_t *max_row) {
+static spk_status plan_common(spk_ctx ctx, const spk_csr *A, spk_plan *out, int64_t *max_row, int64_t chunk = 0,
+                              int64_t *max_chunk = nullptr) {
     if (!ctx || !out) return SPK_ERR_INVALID_ARG;
     *out = nullptr;
     SPK_HIP(ctx, hipSetDevice(ctx->device));
     spk_status s = check_csr_args(ctx, A);
     if (s != SPK_OK) return s;
     int32_t verdict = 0;
-    s = gpu_verdict(ctx, A, &verdict, max_row);
+    s = gpu_verdict(ctx, A, &verdict, max_row, chunk, max_chunk);
     if (s != SPK_OK) return s;
     // SPK_LONG_ROWS=0: every row summed by one lane, however long (comparisons)
     const char *lr = std::getenv("SPK_LONG_ROWS");
@@ -1113,8 +1164,10 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
     if (mixed && (!(cfg.inner_reduction > 0.0) || cfg.inner_reduction >= 1.0))
         return fail(ctx, SPK_ERR_INVALID_ARG, "inner_reduction must be in (0, 1)");
     if (mixed && cfg.max_outer < 0) return fail(ctx, SPK_ERR_INVALID_ARG, "max_outer < 0");
-    int64_t max_row = 0;
-    spk_status s = plan_common(ctx, A, out, &max_row);
+    int64_t max_row = 0, max_chunk = 0;
+    const bool resident = A && A->n_rows > 0 && resident_wanted(ctx, cfg, A->n_rows);
+    const int res_rows = resident ? resident_rows(A->n_rows) : 0;
+    spk_status s = plan_common(ctx, A, out, &max_row, res_rows, &max_chunk);
     if (s != SPK_OK) return s;
     if (A->n_rows != A->n_cols) return fail(ctx, SPK_ERR_INVALID_ARG, "solve needs a square matrix");
     if (!mixed && A->val_type != SPK_F64) return fail(ctx, SPK_ERR_INVALID_ARG, "FP64 precision needs F64 values");
@@ -1275,6 +1328,16 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         pl->tune32 = pl->tune;
         pl->tune = heuristic_tune(ctx, pl->A);
     }
+    if (resident && resident_shape(pl, res_rows, max_chunk, mixed)) {
+        const size_t cb = kResidentCtlBytes;
+        if (!dget(cb, &pl->res_ctl) || !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch) ||
+            (mixed && !dget(sizeof(spk::PersistResult), &pl->persist_res)))
+            return cleanup(SPK_ERR_OUT_OF_MEMORY, "resident solve workspace");
+        if (hipMemsetAsync(pl->res_ctl, 0, cb, ctx->stream) != hipSuccess ||
+            hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess ||
+            (mixed && hipMemsetAsync(pl->persist_res, 0, sizeof(spk::PersistResult), ctx->stream) != hipSuccess))
+            return cleanup(SPK_ERR_DEVICE, "resident solve workspace");
+    }
     int mode = cfg.exec_mode;
     // Automatic choice: the host-issued loop.  On MI355X its launches queue
     // back to back (about 8 us per iteration at the smallest sizes), which
@@ -1433,12 +1496,61 @@ static spk_status run_persistent(spk_plan pl, const double *b, double *x) {
     return SPK_OK;
 }
 
+// One launch for the whole solve, its matrix on the chip.  *done = false: its
+// workgroups could not all start at once (the device is shared), nothing was
+// written, and the caller runs the launch-per-iteration loop instead.
+static spk_status run_resident(spk_plan pl, const double *b, double *x, spk::PersistResult *result, bool *done) {
+    spk_ctx ctx = pl->ctx;
+    const spk_solver_cfg &cfg = pl->cfg;
+    const bool mixed = cfg.precision != SPK_PREC_FP64;
+    spk::ResidentSolve a{};
+    a.rows = pl->res_rows;
+    a.lds_entries = pl->res_lds;
+    a.b = b;
+    a.x = x;
+    a.xch = pl->res_xch;
+    a.ctl = pl->res_ctl;
+    a.slots = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(pl->res_ctl) + 64);
+    a.epoch = ++pl->res_epoch;
+    // 0.2 ms to start; SPK_RESIDENT=refuse: every launch leaves (tests)
+    const char *refuse = std::getenv("SPK_RESIDENT");
+    a.gate_ticks = refuse && std::strcmp(refuse, "refuse") == 0 ? 0 : static_cast<unsigned long long>(ctx->wall_khz) / 5;
+    a.spin_ticks = static_cast<unsigned long long>(ctx->wall_khz) * 2000ull;   // 2 s
+    a.st = pl->st;
+    a.res = pl->persist_res;
+    a.tau = cfg.reduction_factor;
+    a.tau_in = cfg.inner_reduction;
+    a.max_iters = cfg.max_iters;
+    a.max_outer = cfg.max_outer;
+    a.hist = pl->hist;
+    a.hist_cap = pl->hist_cap;
+    a.true_residual = cfg.true_residual;
+    SPK_HIP(ctx, spk::launch_resident(mixed ? pl->A32 : pl->A, mixed ? &pl->A : nullptr, a, pl->res_grid, ctx->stream));
+    unsigned ctl[spk::kResidentCtl] = {};
+    spk_status s = SPK_OK;
+    if (mixed) {
+        if ((s = pull(ctx, result, pl->persist_res, sizeof(*result))) != SPK_OK) return s;
+        *done = result->epoch == a.epoch;
+    } else {
+        if ((s = pull(ctx, pl->h_st, pl->st, sizeof(SolveState))) != SPK_OK) return s;
+        *done = pl->h_st->base == static_cast<int64_t>(a.epoch);
+    }
+    if (*done) return SPK_OK;
+    if ((s = pull(ctx, ctl, pl->res_ctl, sizeof(ctl))) != SPK_OK) return s;
+    if (ctl[3] != 0) return fail(ctx, SPK_ERR_DEVICE, "resident solve: a wait timed out");
+    return SPK_OK;
+}
+
 static spk_status execute_fp64(spk_plan pl, const double *b, double *x, spk_log *L, bool graph) {
     spk_ctx ctx = pl->ctx;
     const spk_solver_cfg &cfg = pl->cfg;
     const int64_t n = pl->A.n_rows;
     spk_status s = SPK_OK;
-    if (pl->right_jacobi && pl->bad_diag) {
+    bool done = false;
+    if (pl->res_grid > 0 && !pl->profiling && (s = run_resident(pl, b, x, nullptr, &done)) != SPK_OK) return s;
+    if (done) {
+        // the state is read back
+    } else if (pl->right_jacobi && pl->bad_diag) {
         // no preconditioner: the initial check reports the breakdown, x unchanged
         SPK_HIP(ctx, spk::launch_pcg_init(pl->A_orig, pl->tune, b, x, pl->dinv, pl->diag_flag, pl->r, pl->p, pl->st,
                                           pl->partials, cfg.reduction_factor, cfg.max_iters, pl->hist, pl->hist_cap,
@@ -1524,11 +1636,19 @@ static spk_status execute_mixed(spk_plan pl, const double *b, double *x, spk_log
     spk_ctx ctx = pl->ctx;
     const spk_solver_cfg &cfg = pl->cfg;
     const int64_t n = pl->A.n_rows;
+    spk::PersistResult r{};
+    bool whole = false;
+    if (pl->res_grid > 0 && !pl->profiling) {
+        spk_status s = run_resident(pl, b, x, &r, &whole);
+        if (s != SPK_OK) return s;
+    }
     if (pl->persist_grid > 0) {
         spk_status s = run_persistent(pl, b, x);
         if (s != SPK_OK) return s;
-        spk::PersistResult r{};
         if ((s = pull(ctx, &r, pl->persist_res, sizeof(r))) != SPK_OK) return s;
+        whole = true;
+    }
+    if (whole) {
         L->iterations = r.inner;
         L->outer_iterations = r.outer;
         L->implicit_resnorm = r.rnorm;
@@ -1688,8 +1808,10 @@ spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg
                         hipGetErrorString(ctx->scratch_err));
     SPK_HIP(ctx, hipSetDevice(ctx->device));
     int32_t verdict = 0;
-    int64_t max_row = 0;
-    if ((s = gpu_verdict(ctx, A, &verdict, &max_row)) != SPK_OK) return s;
+    int64_t max_row = 0, max_chunk = 0;
+    const bool resident = n > 0 && resident_wanted(ctx, cfg, n);
+    const int res_rows = resident ? resident_rows(n) : 0;
+    if ((s = gpu_verdict(ctx, A, &verdict, &max_row, res_rows, &max_chunk)) != SPK_OK) return s;
     if (verdict != SPK_CSR_OK) return fail(ctx, SPK_ERR_INVALID_ARG, std::string("malformed CSR: ") + verdict_name(verdict));
     spk_log L;
     std::memset(&L, 0, sizeof(L));
@@ -1740,6 +1862,16 @@ spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg
     // the scratch keeps the last call's contents: clear the state and p by kernel
     SPK_HIP(ctx, spk::launch_fill_zero(pl.st, na_align(sizeof(SolveState)), ctx->num_cu, ctx->stream));
     SPK_HIP(ctx, spk::launch_fill_zero(pl.p, vb, ctx->num_cu * 4, ctx->stream));
+    if (resident && resident_shape(&pl, res_rows, max_chunk, false)) {
+        // slots in the partials, exchange buffers in r, p and q: the solve
+        // uses neither when it runs as one launch, and when that launch
+        // leaves without a result the loop initialises both
+        pl.res_ctl = reinterpret_cast<unsigned *>(pl.partials);
+        pl.res_xch = pl.r;
+        SPK_HIP(ctx, spk::launch_fill_zero(pl.res_ctl, kResidentCtlBytes, ctx->num_cu, ctx->stream));
+        SPK_HIP(ctx, spk::launch_fill_zero(pl.res_xch, (spk::resident_exchange_bytes(n, false) + 15) & ~size_t(15),
+                                           ctx->num_cu * 4, ctx->stream));
+    }
     SPK_HIP(ctx, hipEventRecord(ctx->ev0, ctx->stream));
     s = execute_fp64(&pl, static_cast<const double *>(b_in), static_cast<double *>(x_in), &L, false);
     if (s != SPK_OK) {

@@ -65,6 +65,41 @@ struct PersistResult {
     int64_t inner, outer;   // inner iterations in all, refinement steps
     double rnorm, bnorm;    // last ||b - A x|| (FP64) and ||b||
     int32_t stop;
+    uint32_t epoch;         // resident solves: the launch that wrote the result
+};
+
+// Resident solves (one launch per solve, the matrix held on the chip).
+constexpr int kResidentRows = 512;      // most rows of a workgroup (one thread each)
+constexpr int kResidentGrid = 256;      // most workgroups (16 groups of 16)
+constexpr int kResidentRegs = 8;        // entries of a row held in registers
+constexpr int kResidentRowMax = 32;     // longest row: one thread works through it
+constexpr size_t kResidentLds = size_t(152) << 10;   // LDS for the rows' other entries (of 160 KB per CU)
+constexpr int kResidentTurns = 4;       // sets of exchange words used in turn
+constexpr int kResidentSlots = kResidentTurns * (8 + 16) * 4 * 16;   // words of the grid sums
+constexpr int kResidentCtl = 8;         // control words
+
+// Arguments of a resident solve (matrix fields and xd filled by the launcher).
+struct ResidentSolve {
+    int64_t n;
+    const void *rp, *ci, *va, *va64;
+    int ptr_t, idx_t;
+    int rows;                 // consecutive rows per workgroup
+    int lds_entries;          // most entries of a workgroup, 0 when no row is longer than the registers hold
+    const double *b;
+    double *x;
+    void *xch;                // exchange buffers (resident_exchange_bytes), zero before the first launch
+    double *xd;
+    unsigned long long *slots;   // kResidentSlots words, zero before the first launch
+    unsigned *ctl;            // kResidentCtl words, zero before the first launch
+    unsigned epoch;           // 1, 2, ... per launch on these control words
+    unsigned long long gate_ticks, spin_ticks;   // wall-clock limits of the start and of one wait
+    SolveState *st;           // FP64 solve: the state the host reads (base = epoch once done)
+    PersistResult *res;       // mixed solve: the result
+    double tau, tau_in;
+    int64_t max_iters, max_outer;
+    double *hist;
+    int64_t hist_cap;
+    int true_residual;
 };
 
 // Arguments of a persistent solve (matrix fields filled by the launcher).

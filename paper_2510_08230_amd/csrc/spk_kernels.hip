@@ -456,13 +456,18 @@ constexpr int kValidateUnroll = 4;
 template <typename P, typename I>
 __global__ __launch_bounds__(kBlock) void k_validate(int64_t n_rows, int64_t n_cols, int64_t nnz,
                                                      const P *__restrict__ rp, const I *__restrict__ ci,
-                                                     unsigned *flags) {
+                                                     unsigned *flags, int64_t chunk) {
     unsigned f = 0;
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     if (gid == 0) {
         if (rp[0] != 0) f |= VFLAG_BAD_FIRST;
         if (static_cast<int64_t>(rp[n_rows]) != nnz) f |= VFLAG_BAD_LAST;
+    }
+    if (chunk > 0 && gid * chunk < n_rows) {   // few chunks, one thread each (the grid covers them)
+        const int64_t i = gid * chunk;
+        const int64_t len = static_cast<int64_t>(rp[min(i + chunk, n_rows)]) - static_cast<int64_t>(rp[i]);
+        if (len > 0) atomicMax(flags + 2, len > 0xffffffffll ? 0xffffffffu : static_cast<unsigned>(len));
     }
     // Both walks take kValidateUnroll strides per round with every load of
     // the round issued before the first check, so each lane keeps that many
@@ -928,13 +933,14 @@ int grid_for(int64_t n, int per_thread, int cap) {
 }  // namespace
 
 // ==================================================================== launchers
-hipError_t launch_validate(const CsrDev &A, unsigned *flags, int max_grid, hipStream_t s) {
+hipError_t launch_validate(const CsrDev &A, unsigned *flags, int64_t chunk, int max_grid, hipStream_t s) {
     const int64_t work = A.n_rows > A.nnz ? A.n_rows : A.nnz;
     const int grid = grid_for(work, 8, max_grid);
+    if (chunk > 0 && chunk * grid * kBlock < A.n_rows) return hipErrorInvalidValue;
     return dispatch_idx(A, [&](auto rp, auto ci) {
         using P = pointee_t<decltype(rp)>;
         using I = pointee_t<decltype(ci)>;
-        hipLaunchKernelGGL((k_validate<P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, A.n_cols, A.nnz, rp, ci, flags);
+        hipLaunchKernelGGL((k_validate<P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, A.n_cols, A.nnz, rp, ci, flags, chunk);
         return hipGetLastError();
     });
 }

@@ -9,8 +9,10 @@ namespace spk {
 
 // ---- launchers (spk_kernels.hip) -------------------------------------------------
 // CSR checks: flags[0] |= VFLAG_* bits, flags[1] = max(flags[1], the longest
-// row's entry count, clamped to 2^32 - 1); both words zero before the launch.
-hipError_t launch_validate(const CsrDev &A, unsigned *flags, int max_grid, hipStream_t s);
+// row's entry count, clamped to 2^32 - 1) and, with chunk > 0, flags[2] = the
+// same of the entries of chunk consecutive rows (rows 0, chunk, 2 chunk, ...
+// on); the words zero before the launch.
+hipError_t launch_validate(const CsrDev &A, unsigned *flags, int64_t chunk, int max_grid, hipStream_t s);
 hipError_t launch_partition(const CsrDev &A, int64_t parts, int64_t *split, hipStream_t s);
 // The distinct column offsets c - i of every step-th row tile (and the last)
 // collected into table (kCodeSlots slots); words[0] counts them, words[1] is
@@ -170,6 +172,17 @@ hipError_t launch_pcg_pupdate(int64_t n, int grid, int j, const double *r, const
 // solve writes a.res.
 hipError_t launch_persistent(const CsrDev &A, const CsrDev *outer, PersistSolve a, int grid, hipStream_t s);
 int persistent_blocks_per_cu(const CsrDev &A, const CsrDev *outer);
+
+// ---- launchers (spk_resident.hip) ------------------------------------------------
+// Resident solves: workgroup g holds rows [g * rows, (g + 1) * rows).
+size_t resident_lds_bytes(int64_t entries, bool mixed);
+size_t resident_exchange_bytes(int64_t n, bool mixed);
+// outer: the refinement's matrix of a mixed solve (same index arrays as A,
+// whose values are the inner solve's), nullptr for an FP64 solve on A.  The
+// launch leaves without a result (a.st->base / a.res->epoch is not a.epoch)
+// when its workgroups could not all start, or sets a.ctl[3] when a wait timed
+// out.
+hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, int grid, hipStream_t s);
 
 // Workgroups of the SpMV kernel resident per CU for this tune/type (occupancy API).
 int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t);

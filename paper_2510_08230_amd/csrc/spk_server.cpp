@@ -168,7 +168,7 @@ bool request_valid(spk_server srv, const Request &r) {
     spk::CsrDev d{r.A.n_rows, r.A.n_cols, r.A.nnz, r.A.ptr_type, r.A.idx_type, r.A.val_type,
                   r.A.row_ptr, r.A.col_idx, r.A.values};
     if (!hip_ok(srv, hipMemsetAsync(srv->d_flags, 0, 2 * sizeof(unsigned), srv->stream), "flags")) return false;
-    if (!hip_ok(srv, spk::launch_validate(d, srv->d_flags, srv->num_cu * 4, srv->stream), "validate")) return false;
+    if (!hip_ok(srv, spk::launch_validate(d, srv->d_flags, 0, srv->num_cu * 4, srv->stream), "validate")) return false;
     if (!hip_ok(srv, hipMemcpyAsync(srv->h_flags, srv->d_flags, sizeof(unsigned), hipMemcpyDeviceToHost, srv->stream),
                 "flags copy"))
         return false;
