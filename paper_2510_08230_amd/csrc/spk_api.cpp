@@ -94,6 +94,7 @@ struct spk_plan_s {
     double *rt = nullptr, *u = nullptr, *v = nullptr, *uh = nullptr;   // CGS
     double *dinv = nullptr;              // Jacobi: 1 / diag(A)
     void *coo_rp = nullptr;              // COO SpMV: derived row pointer (owned)
+    void *long_buf = nullptr;            // long rows' pieces, their sums and each row's first piece (owned)
     void *codes_buf = nullptr;           // column codes: offset table + one byte per entry (owned)
     void *gm_V = nullptr, *gm_w = nullptr;   // GMRES basis and work vector (FP64, or FP32 in GMRES-IR)
     double *gm_part = nullptr;               // GMRES per-workgroup partials
@@ -488,6 +489,46 @@ spk_status build_codes(spk_plan pl) {
     return SPK_OK;
 }
 
+// The pieces of the rows longer than kLongRow (k_long_pieces), for matrices
+// whose products run on row tiles (the autotuner's rule).  max_row has to be
+// known.  Without memory for them the tiles sum such rows themselves.
+spk_status build_pieces(spk_plan pl) {
+    spk_ctx ctx = pl->ctx;
+    CsrDev &A = pl->A;
+    if (A.max_row <= spk::kLongRow || A.nnz > 64 * A.n_rows || A.n_rows > INT32_MAX || !stream_ok(A)) return SPK_OK;
+    // every long row has at most len / kLongPiece + 1 pieces and more than kLongRow entries
+    const int64_t cap = A.nnz / spk::kLongPiece + A.nnz / spk::kLongRow + 1;
+    if (cap > INT32_MAX) return SPK_OK;
+    auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
+    const size_t lb = up(sizeof(spk::LongPiece) * cap), sb = up(sizeof(double) * cap);
+    const size_t bb = up(sizeof(int32_t) * static_cast<size_t>(A.n_rows));
+    void *buf = nullptr;
+    if (ctx->dpool.get(lb + sb + bb, &buf) != hipSuccess) return SPK_OK;
+    char *base = static_cast<char *>(buf);
+    auto *pieces = reinterpret_cast<spk::LongPiece *>(base);
+    auto *first = reinterpret_cast<int32_t *>(base + lb + sb);
+    if (hipMemsetAsync(ctx->d_flags, 0, 2 * sizeof(unsigned), ctx->stream) != hipSuccess ||
+        spk::launch_long_list(A, pieces, static_cast<int>(cap), first, ctx->d_flags, ctx->num_cu * 4, ctx->stream) !=
+            hipSuccess ||
+        hipMemcpyAsync(ctx->h_flags, ctx->d_flags, 2 * sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream) !=
+            hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess) {
+        ctx->dpool.put(buf);
+        return fail(ctx, SPK_ERR_DEVICE, "long rows");
+    }
+    const int64_t np = ctx->h_flags[0];
+    if (np < 1 || np > cap) {
+        ctx->dpool.put(buf);
+        return SPK_OK;
+    }
+    pl->long_buf = buf;
+    A.pieces = pieces;
+    A.n_pieces = static_cast<int>(np);
+    A.piece_sums = reinterpret_cast<double *>(base + lb);
+    A.long_base = first;
+    return SPK_OK;
+}
+
 // ------------------------------------------------------------------ profiling events
 // idx (optional): the recorded launch's event index, -1 when not sampled.
 spk_status prof_begin(spk_plan pl, hipEvent_t *end_ev, int64_t *idx = nullptr) {
@@ -847,6 +888,8 @@ void release_workspace(spk_plan pl) {
     ctx->dpool.put(pl->dinv);
     ctx->dpool.put(pl->diag_flag);
     ctx->dpool.put(pl->coo_rp);
+    ctx->dpool.put(pl->long_buf);
+    pl->long_buf = nullptr;
     ctx->dpool.put(pl->codes_buf);
     pl->codes_buf = nullptr;
     ctx->dpool.put(pl->scaled_vals);
@@ -1103,6 +1146,19 @@ spk_status spk_plan_spmv_coo(spk_ctx ctx, const spk_coo *A, spk_plan *out) {
         return fail(ctx, SPK_ERR_DEVICE, "COO row pointer");
     }
     pl->A = to_dev(&csr);
+    // the longest row (the CSR plans' validation reports it)
+    unsigned words[2] = {0, 0};
+    if (hipMemsetAsync(ctx->d_flags, 0, 2 * sizeof(unsigned), ctx->stream) != hipSuccess ||
+        spk::launch_long_list(pl->A, nullptr, 0, nullptr, ctx->d_flags, ctx->num_cu * 4, ctx->stream) != hipSuccess ||
+        hipMemcpyAsync(words, ctx->d_flags, sizeof(words), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess) {
+        (void)hipStreamSynchronize(ctx->stream);
+        release_workspace(pl);
+        delete pl;
+        return fail(ctx, SPK_ERR_DEVICE, "COO row lengths");
+    }
+    const char *lr = std::getenv("SPK_LONG_ROWS");
+    pl->A.max_row = lr && std::strcmp(lr, "0") == 0 ? 0 : words[1];
     return finish_spmv_plan(ctx, pl, &csr, out);
 }
 
@@ -1124,6 +1180,7 @@ static spk_status finish_spmv_plan(spk_ctx ctx, spk_plan pl, const spk_csr *A, s
         (void)hipMemsetAsync(x, 0, A->n_cols * vb, ctx->stream);
     }
     s = build_codes(pl);
+    if (s == SPK_OK) s = build_pieces(pl);
     if (s == SPK_OK) s = choose_tune(pl, x, y);
     (void)hipStreamSynchronize(ctx->stream);
     ctx->dpool.put(x);
@@ -1213,6 +1270,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
     if (fused_needs_pattern(cfg, n) && (s = pattern_regular(ctx, pl->A, &regular)) != SPK_OK)
         return cleanup(s, ctx->err);
     s = build_codes(pl);
+    if (s == SPK_OK) s = build_pieces(pl);
     if (s != SPK_OK) return cleanup(s, ctx->err);
     const int64_t want = (n + int64_t(spk::kBlock) * 8 - 1) / (int64_t(spk::kBlock) * 8);
     // Streaming kernels: 4 workgroups per CU measured best for HBM copy rates.

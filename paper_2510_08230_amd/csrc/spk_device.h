@@ -375,12 +375,28 @@ __device__ __forceinline__ C row_from_lds(const V *sv, const I *sc, int64_t a, i
     return sum;
 }
 
-template <typename V, typename I, typename C, class Gx, class D = ColPlain>
+// The same from global memory, U entries' loads in flight at a time.
+template <typename V, typename I, typename C, int U = 1, class Gx, class D = ColPlain>
 __device__ __forceinline__ C row_from_global(const V *__restrict__ va, const I *__restrict__ ci, int64_t a, int64_t b,
                                              const Gx &gx, int nt, const D &col = D{}, int64_t row = 0) {
     C sum = 0;
-    for (int64_t k = a; k < b; ++k)
-        sum = fma(static_cast<C>(widen(ldv(va + k, nt))), static_cast<C>(gx(col(ci[k], row))), sum);
+    if constexpr (U == 1) {
+        for (int64_t k = a; k < b; ++k)
+            sum = fma(static_cast<C>(widen(ldv(va + k, nt))), static_cast<C>(gx(col(ci[k], row))), sum);
+    } else {
+        for (int64_t k0 = a; k0 < b; k0 += U) {
+            C av[U], xv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = k0 + u < b ? k0 + u : b - 1;
+                av[u] = static_cast<C>(widen(ldv(va + k, nt)));
+                xv[u] = static_cast<C>(gx(col(ci[k], row)));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + u < b) sum = fma(av[u], xv[u], sum);
+        }
+    }
     return sum;
 }
 

@@ -171,9 +171,26 @@ struct CsrDev {
     // unknown).  Above kLongRow the row tiles sum such rows with the whole
     // workgroup (host side only: it sets the kernels' long-row argument).
     int64_t max_row = 0;
+    // Optional pieces of the rows longer than kLongRow (null when absent): at
+    // most kLongPiece entries each, summed by a launch of their own ahead of
+    // the row tiles (sums[p] = piece p's); a long row's pieces are consecutive
+    // from long_base[row] on.
+    const struct LongPiece *pieces = nullptr;
+    int n_pieces = 0;
+    const int32_t *long_base = nullptr;
+    double *piece_sums = nullptr;
 };
 
-constexpr int kLongRow = 256;   // rows longer than this are summed by a whole workgroup
+constexpr int kLongRow = 256;   // rows longer than this are summed by whole workgroups
+// Entries of a long row that one workgroup sums at once: 4 per thread, all of
+// their loads in flight together.
+constexpr int kLongPiece = 1024;
+
+struct LongPiece {
+    int64_t first;   // entry
+    int32_t len;
+    int32_t row;
+};
 
 constexpr int kCodeDict = 256;    // distinct column offsets a code table holds
 constexpr int kCodeSlots = 1024;  // plan-time hash table of distinct offsets (power of two)

@@ -870,6 +870,31 @@ __global__ __launch_bounds__(kBlock) void k_coo_rowptr(int64_t n_rows, int64_t n
     }
 }
 
+// Pieces of the rows longer than kLongRow, and the longest row: words[0] =
+// pieces (those past cap are counted, not stored), words[1] = the longest
+// row's entries.  The rows' order in the list varies from run to run; a row's
+// own pieces are consecutive and in order.
+template <typename P>
+__global__ __launch_bounds__(kBlock) void k_long_list(int64_t n, const P *__restrict__ rp, LongPiece *pieces, int cap,
+                                                      int32_t *base, unsigned *words) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+    unsigned longest = 0;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) {
+        const int64_t a = static_cast<int64_t>(rp[i]), len = static_cast<int64_t>(rp[i + 1]) - a;
+        longest = max(longest, static_cast<unsigned>(min(len, static_cast<int64_t>(0xffffffff))));
+        if (len <= kLongRow || !pieces) continue;
+        const int64_t np = (len + kLongPiece - 1) / kLongPiece;
+        const int64_t at = atomicAdd(words, static_cast<unsigned>(np));
+        base[i] = static_cast<int32_t>(at);
+        for (int64_t p = 0; p < np && at + p < cap; ++p) {
+            const int64_t first = a + p * kLongPiece;
+            pieces[at + p] = LongPiece{first, static_cast<int32_t>(min(static_cast<int64_t>(kLongPiece), a + len - first)),
+                                       static_cast<int32_t>(i < INT32_MAX ? i : 0)};
+        }
+    }
+    if (longest > __hip_atomic_load(words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(words + 1, longest);
+}
+
 template <typename P>
 __global__ __launch_bounds__(kBlock) void k_partition(int64_t n, const P *__restrict__ rp, int64_t parts,
                                                       int64_t *split) {
@@ -1009,6 +1034,18 @@ hipError_t launch_coo_rowptr(int64_t n_rows, int64_t nnz, const void *row, int i
     else
         hipLaunchKernelGGL((k_coo_rowptr<int64_t, int64_t>), dim3(grid), dim3(kBlock), 0, s, n_rows, nnz,
                            static_cast<const int64_t *>(row), static_cast<int64_t *>(rp));
+    return hipGetLastError();
+}
+
+hipError_t launch_long_list(const CsrDev &A, LongPiece *pieces, int cap, int32_t *base, unsigned *words, int max_grid,
+                            hipStream_t s) {
+    const int grid = grid_for(A.n_rows, 4, max_grid);
+    if (A.ptr_t == 0)
+        hipLaunchKernelGGL((k_long_list<int32_t>), dim3(grid), dim3(kBlock), 0, s, A.n_rows,
+                           static_cast<const int32_t *>(A.rp), pieces, cap, base, words);
+    else
+        hipLaunchKernelGGL((k_long_list<int64_t>), dim3(grid), dim3(kBlock), 0, s, A.n_rows,
+                           static_cast<const int64_t *>(A.rp), pieces, cap, base, words);
     return hipGetLastError();
 }
 
@@ -1243,14 +1280,14 @@ int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t) {
         if (t.kind == 0) {
             if (i64) {
                 q2(k_spmv_stream<double, int64_t, int64_t, double, double, EpiPq<double>>,
-                   k_spmv_stream<double, int64_t, int64_t, double, double, EpiPq<double>, true>);
+                   k_spmv_stream<double, int64_t, int64_t, double, double, EpiPq<double>, 2>);
                 q2(k_spmv_stream<double, int64_t, int64_t, double, double, EpiPlain<double>>,
-                   k_spmv_stream<double, int64_t, int64_t, double, double, EpiPlain<double>, true>);
+                   k_spmv_stream<double, int64_t, int64_t, double, double, EpiPlain<double>, 2>);
             } else {
                 q2(k_spmv_stream<double, int64_t, int32_t, double, double, EpiPq<double>>,
-                   k_spmv_stream<double, int64_t, int32_t, double, double, EpiPq<double>, true>);
+                   k_spmv_stream<double, int64_t, int32_t, double, double, EpiPq<double>, 2>);
                 q2(k_spmv_stream<double, int64_t, int32_t, double, double, EpiPlain<double>>,
-                   k_spmv_stream<double, int64_t, int32_t, double, double, EpiPlain<double>, true>);
+                   k_spmv_stream<double, int64_t, int32_t, double, double, EpiPlain<double>, 2>);
             }
         } else {
             if (i64) {
@@ -1264,9 +1301,9 @@ int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t) {
     } else {
         if (t.kind == 0) {
             q2(k_spmv_stream<float, int64_t, int32_t, float, float, EpiPlain<float>>,
-               k_spmv_stream<float, int64_t, int32_t, float, float, EpiPlain<float>, true>);
+               k_spmv_stream<float, int64_t, int32_t, float, float, EpiPlain<float>, 2>);
             q2(k_spmv_stream<float, int64_t, int32_t, float, float, EpiPq<float>>,
-               k_spmv_stream<float, int64_t, int32_t, float, float, EpiPq<float>, true>);
+               k_spmv_stream<float, int64_t, int32_t, float, float, EpiPq<float>, 2>);
         } else {
             q(k_spmv_vector<float, int64_t, int32_t, float, float, EpiPlain<float>>);
             q(k_spmv_vector<float, int64_t, int32_t, float, float, EpiPq<float>>);

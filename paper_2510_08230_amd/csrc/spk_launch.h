@@ -14,6 +14,11 @@ namespace spk {
 // on); the words zero before the launch.
 hipError_t launch_validate(const CsrDev &A, unsigned *flags, int64_t chunk, int max_grid, hipStream_t s);
 hipError_t launch_partition(const CsrDev &A, int64_t parts, int64_t *split, hipStream_t s);
+// Pieces of A's rows longer than kLongRow (pieces null: none listed) and the
+// longest row: words[0] counts pieces (cap of them are stored), words[1] is
+// the longest row's entries; both zero before the launch.
+hipError_t launch_long_list(const CsrDev &A, LongPiece *pieces, int cap, int32_t *base, unsigned *words, int max_grid,
+                            hipStream_t s);
 // The distinct column offsets c - i of every step-th row tile (and the last)
 // collected into table (kCodeSlots slots); words[0] counts them, words[1] is
 // set when there are more than kCodeDict.  A must be valid.

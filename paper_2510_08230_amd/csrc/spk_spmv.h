@@ -53,20 +53,51 @@ __device__ __forceinline__ void row_range<RowPack>(const RowPack *__restrict__ r
     b = row + 1 < r1 ? tb[tile] + ro[row + 1] : tb[tile + 1];
 }
 
+// Sum of entries [a, b) of one row (b - a <= kLongPiece) by the whole
+// workgroup, the same in every thread: each thread its strided share in
+// storage order with every load in flight before the first use, then the wave
+// sums and the four wave totals in a fixed order.  val(k) / cix(k): entry k's
+// value and stored column.  Every thread of the workgroup calls this.
+template <typename C, class Gx, class D, class Val, class Cix>
+__device__ __forceinline__ C piece_sum(int64_t a, int64_t b, int64_t row, const Gx &gx, const D &col, const Val &val,
+                                       const Cix &cix) {
+    __shared__ C s_red[kBlock / 64];
+    constexpr int U = kLongPiece / kBlock;
+    C av[U], xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t k = a + threadIdx.x + u * kBlock;
+        const int64_t kc = k < b ? k : b - 1;   // every lane loads
+        av[u] = static_cast<C>(widen(val(kc)));
+        xv[u] = static_cast<C>(gx(col(cix(kc), row)));
+    }
+    C acc = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (a + threadIdx.x + u * kBlock < b) acc = fma(av[u], xv[u], acc);
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    C t = s_red[0];
+#pragma unroll
+    for (int v = 1; v < kBlock / 64; ++v) t += s_red[v];
+    __syncthreads();   // s_red is reused by the next piece
+    return t;
+}
+
 // The rows of the tile at r0 whose flag lng is set (rows longer than the
 // long-row limit), summed one at a time by the whole workgroup in ascending
-// row order -- each thread a strided share in storage order, then the wave
-// sums and the four wave totals in a fixed order -- and handed to epi.row by
-// the row's own thread.  Every thread of the workgroup calls this (it
-// synchronises); the flags go through LDS as one ballot per wave, so nothing
-// of the per-lane row loop stays live for it.  val(k) / cix(k): entry k's
-// value and stored column (read from global memory, also for a tile staged
-// in LDS: one call site keeps the kernel's register count down).
+// row order, piece by piece, and handed to epi.row by the row's own thread
+// (for products that form their input vector on the fly; the others have
+// their pieces summed ahead, k_long_pieces, in the same order).  Every thread
+// of the workgroup calls this (it synchronises); the flags go through LDS as
+// one ballot per wave, so nothing of the per-lane row loop stays live for it.
+// val(k) / cix(k) read global memory, also for a tile staged in LDS: one call
+// site keeps the kernel's register count down.
 template <typename C, typename P, class Gx, class D, class Epi, class Val, class Cix>
 __device__ __forceinline__ void long_rows(bool lng, const P *__restrict__ rp, int64_t n, int64_t r0, const Gx &gx,
                                           const D &col, Epi &epi, const Val &val, const Cix &cix) {
     __shared__ unsigned long long s_mask[kBlock / 64];
-    __shared__ C s_red[kBlock / 64];
     const unsigned long long m = __ballot(lng);
     if ((threadIdx.x & 63) == 0) s_mask[threadIdx.x >> 6] = m;
     __syncthreads();
@@ -81,22 +112,31 @@ __device__ __forceinline__ void long_rows(bool lng, const P *__restrict__ rp, in
             row_range(rp, n, row, ra, rb);
             C acc = 0;
 #pragma unroll 1
-            for (int64_t k = ra + threadIdx.x; k < rb; k += kBlock)
-                acc = fma(static_cast<C>(widen(val(k))), static_cast<C>(gx(col(cix(k), row))), acc);
-            acc = wave_sum(acc);
-            if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = acc;
-            __syncthreads();
-            if (static_cast<int>(threadIdx.x) == i) {
-                C t = s_red[0];
-#pragma unroll
-                for (int v = 1; v < kBlock / 64; ++v) t += s_red[v];
-                epi.row(row, t);
-            }
-            __syncthreads();   // s_red is reused by the next long row
+            for (int64_t k = ra; k < rb; k += kLongPiece)
+                acc += piece_sum<C>(k, k + kLongPiece < rb ? k + kLongPiece : rb, row, gx, col, val, cix);
+            if (static_cast<int>(threadIdx.x) == i) epi.row(row, acc);
         }
     }
     __syncthreads();           // s_mask is rewritten by the next tile
 }
+
+// What a kernel needs of the long rows' pieces: nothing unless its LR is 2.
+template <int LR>
+struct LongArg {};
+template <>
+struct LongArg<2> {
+    const int32_t *base;
+    const double *sums;
+    // a long row's sum, from its pieces in order
+    template <typename C>
+    __device__ __forceinline__ C sum(int64_t row, int64_t len) const {
+        const int32_t at = base[row];
+        const int np = static_cast<int>((len + kLongPiece - 1) / kLongPiece);
+        C t = 0;
+        for (int p = 0; p < np; ++p) t += static_cast<C>(sums[at + p]);
+        return t;
+    }
+};
 
 // Epilogue operands loaded with the tile: an epilogue that reads a vector at
 // its row (p_i for p.q, b_i for a residual) may provide pre(i), returning
@@ -128,16 +168,18 @@ __device__ __forceinline__ void emit_row(Epi &epi, int64_t i, C sum, const Pv &p
 // The tile loop of the LDS-staged SpMV, shared by the per-launch kernel and the
 // persistent CG kernel: calls epi.row(row, sum) for every row of the tiles
 // this workgroup visits.  lv / lc: the workgroup's LDS staging buffers.
-// LR (the matrix has rows longer than kLongRow entries): those rows are
+// LR (the matrix has rows longer than kLongRow entries): 1: those rows are
 // summed by the whole workgroup (long_rows), so a hub row does not serialise
-// its tile on one lane.  A compile-time switch: the pass costs registers, and
-// with it in every instance the kernels without hub rows lost a workgroup per
-// CU.
-template <typename V, typename P, typename I, typename C, bool LR, class Gx, class Epi, class D = ColPlain>
+// its tile on one lane; 2: their pieces have been summed by an earlier launch
+// (lra), so a tile with a hub row is not the launch's tail either.  A
+// compile-time switch: the passes cost registers, and with one in every
+// instance the kernels without hub rows lost a workgroup per CU.
+template <typename V, typename P, typename I, typename C, int LR, class Gx, class Epi, class D = ColPlain>
 __device__ __forceinline__ void spmv_tiles_lds(int64_t n, int64_t nnz, const P *__restrict__ rp,
                                                const I *__restrict__ ci, const V *__restrict__ va, const Gx &gx,
                                                int remap, int nt, int pf, Epi &epi, u32x4 *lv, u32x4 *lc,
-                                               const D &col = D{}, uint32_t walkers = 0) {
+                                               const D &col = D{}, uint32_t walkers = 0,
+                                               const LongArg<LR> &lra = LongArg<LR>{}) {
     const V *sv = reinterpret_cast<const V *>(lv);
     const I *sc = reinterpret_cast<const I *>(lc);
     const int64_t T = (n + kTileRows - 1) / kTileRows;
@@ -155,7 +197,7 @@ __device__ __forceinline__ void spmv_tiles_lds(int64_t n, int64_t nnz, const P *
         const int64_t row = cur.r0 + threadIdx.x;
         const int64_t s = cur.first(), e = cur.end();
         const int64_t a = cur.lo(), b = cur.hi();
-        const bool lng = LR && row < r1 && b - a > kLongRow;
+        const bool lng = LR != 0 && row < r1 && b - a > kLongRow;
         if (e - s <= kStreamCap) {
             dma_chunks<V>(va, s, e, nnz, lv, nt);
             dma_chunks<I>(ci, s, e, nnz, lc, nt);
@@ -175,9 +217,13 @@ __device__ __forceinline__ void spmv_tiles_lds(int64_t n, int64_t nnz, const P *
         } else {
             if (more && pf) nxt.load(rp, n, after.tile());
             const auto pv = pre_of(epi, row < r1 ? row : r1 - 1);
-            if (row < r1 && !lng) emit_row(epi, row, row_from_global<V, I, C>(va, ci, a, b, gx, nt, col, row), pv);
+            if (row < r1 && !lng)
+                emit_row(epi, row, row_from_global<V, I, C, LR == 2 ? kRowUnroll : 1>(va, ci, a, b, gx, nt, col, row), pv);
         }
-        if constexpr (LR)
+        if constexpr (LR == 2) {
+            if (lng) epi.row(row, lra.template sum<C>(row, b - a));
+        }
+        if constexpr (LR == 1)
             long_rows<C>(lng, rp, n, cur.r0, gx, col, epi, [&](int64_t k) { return ldv(va + k, nt); },
                          [&](int64_t k) { return ci[k]; });
         if (!more) break;
@@ -223,11 +269,11 @@ constexpr int spmv_min_waves() {
 // when the first ones finish and walk their tiles alone.  They take no
 // tiles instead and store zero partials, so a consumer still sums one
 // partial per launched workgroup and gets the same total.
-template <typename V, typename P, typename I, typename X, typename C, class Epi, bool LR = false>
+template <typename V, typename P, typename I, typename X, typename C, class Epi, int LR = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(spmv_min_waves<V, P, Epi>()))) void k_spmv_stream(int64_t n, int64_t nnz, const P *__restrict__ rp,
                                                         const I *__restrict__ ci, const V *__restrict__ va,
                                                         const X *__restrict__ x, int remap, int nt, int pf,
-                                                        int walkers, Epi epi_in) {
+                                                        int walkers, Epi epi_in, LongArg<LR> lra) {
     Epi epi = epi_in;
     if (epi.skip()) return;
     const uint32_t W = walkers > 0 && static_cast<uint32_t>(walkers) < gridDim.x ? walkers : gridDim.x;
@@ -247,9 +293,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(spmv_min
                                        ColCoded{dict}, W);
     } else {
         spmv_tiles_lds<V, P, I, C, LR>(n, nnz, rp, ci, va, gather_of<X, C>(epi, x), remap, nt, pf, epi, lv, lc,
-                                       ColPlain{}, W);
+                                       ColPlain{}, W, lra);
     }
     epi.finish();
+}
+
+// Sums of the long rows' pieces, one workgroup each, ahead of the row tiles.
+// A hub row of 10^4 entries otherwise holds up its tile's workgroup (or, in
+// the lanes-per-row kernel, its lanes) long after the rest of the matrix is
+// done: 205-250 us for a product of 7.1e6 FP16 entries with 16 hubs, now 54, of
+// which the other rows take 38.
+template <typename V, typename I, typename X, typename C, class Epi>
+__global__ __launch_bounds__(kBlock) void k_long_pieces(const LongPiece *__restrict__ pieces, int np,
+                                                        const I *__restrict__ ci, const V *__restrict__ va,
+                                                        const X *__restrict__ x, int nt, double *__restrict__ sums,
+                                                        Epi epi) {
+    if (epi.skip()) return;
+    const PlainGather<X, C> gx{x};
+    for (int p = blockIdx.x; p < np; p += gridDim.x) {
+        const LongPiece pc = pieces[p];
+        const C t = piece_sum<C>(pc.first, pc.first + pc.len, pc.row, gx, ColPlain{},
+                                 [&](int64_t k) { return ldv(va + k, nt); }, [&](int64_t k) { return ci[k]; });
+        if (threadIdx.x == 0) sums[p] = static_cast<double>(t);
+    }
 }
 
 template <typename V, typename P, typename I, typename C, class Gx, class Epi>
@@ -340,19 +406,29 @@ hipError_t launch_family(const CsrDev &A, const SpmvTune &t, const X *x, const E
         } else if (coded && t.pack && A.rowpack) {
             constexpr auto K = k_spmv_stream<V, RowPack, Code8, X, C, Epi>;
             hipLaunchKernelGGL(K, grid, block, 0, s, A.n_rows, A.nnz, static_cast<const RowPack *>(A.rowpack),
-                               static_cast<const Code8 *>(A.codes), va, x, t.xcd_remap, t.nt, t.pf, walkers(resident_per_cu<K>()), epi);
+                               static_cast<const Code8 *>(A.codes), va, x, t.xcd_remap, t.nt, t.pf, walkers(resident_per_cu<K>()), epi, LongArg<0>{});
         } else if (coded) {
             constexpr auto K = k_spmv_stream<V, P, Code8, X, C, Epi>;
             hipLaunchKernelGGL(K, grid, block, 0, s, A.n_rows, A.nnz, rp, static_cast<const Code8 *>(A.codes), va, x,
-                               t.xcd_remap, t.nt, t.pf, walkers(resident_per_cu<K>()), epi);
+                               t.xcd_remap, t.nt, t.pf, walkers(resident_per_cu<K>()), epi, LongArg<0>{});
         } else if (t.kind == 0 && lr) {
-            constexpr auto K = k_spmv_stream<V, P, I, X, C, Epi, true>;
+            if constexpr (!HasGather<Epi>::value) {
+                if (A.pieces) {
+                    hipLaunchKernelGGL((k_long_pieces<V, I, X, C, Epi>), dim3(std::min(A.n_pieces, kMaxGrid)), block, 0,
+                                       s, A.pieces, A.n_pieces, ci, va, x, t.nt, A.piece_sums, epi);
+                    constexpr auto K2 = k_spmv_stream<V, P, I, X, C, Epi, 2>;
+                    hipLaunchKernelGGL(K2, grid, block, 0, s, A.n_rows, A.nnz, rp, ci, va, x, t.xcd_remap, t.nt, t.pf,
+                                       walkers(resident_per_cu<K2>()), epi, LongArg<2>{A.long_base, A.piece_sums});
+                    return hipGetLastError();
+                }
+            }
+            constexpr auto K = k_spmv_stream<V, P, I, X, C, Epi, 1>;
             hipLaunchKernelGGL(K, grid, block, 0, s, A.n_rows, A.nnz, rp, ci, va, x, t.xcd_remap, t.nt, t.pf,
-                               walkers(resident_per_cu<K>()), epi);
+                               walkers(resident_per_cu<K>()), epi, LongArg<1>{});
         } else if (t.kind == 0) {
             constexpr auto K = k_spmv_stream<V, P, I, X, C, Epi>;
             hipLaunchKernelGGL(K, grid, block, 0, s, A.n_rows, A.nnz, rp, ci, va, x, t.xcd_remap, t.nt, t.pf,
-                               walkers(resident_per_cu<K>()), epi);
+                               walkers(resident_per_cu<K>()), epi, LongArg<0>{});
         } else {
             hipLaunchKernelGGL((k_spmv_vector<V, P, I, X, C, Epi>), grid, block, 0, s, A.n_rows, rp, ci, va, x,
                                t.lanes_log2, t.xcd_remap, t.nt, epi);
