@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libspk.so")
 OBJ = os.path.join(PKG, "_build")
 SOURCES = ["spk_kernels.hip", "spk_krylov.hip", "spk_gmres.hip", "spk_batch.hip", "spk_persist.hip", "spk_resident.hip",
-           "spk_noalloc.hip", "spk_api.cpp", "spk_server.cpp"]
+           "spk_split.hip", "spk_noalloc.hip", "spk_api.cpp", "spk_server.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

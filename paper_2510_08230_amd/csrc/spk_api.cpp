@@ -14,6 +14,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <tuple>
 #include <type_traits>
@@ -32,9 +33,10 @@ struct TuneKey {
     int codes;   // the matrix has column codes
     int staged;  // values and columns are 16-byte aligned (the LDS tiles may run)
     int long_rows;    // rows longer than kLongRow (the kernels with the long-row pass run)
+    int split;        // the plan may split the gathers (split_rule)
     bool operator<(const TuneKey &o) const {
-        return std::tie(n_rows, n_cols, nnz, pt, it, vt, use, codes, staged, long_rows) <
-               std::tie(o.n_rows, o.n_cols, o.nnz, o.pt, o.it, o.vt, o.use, o.codes, o.staged, o.long_rows);
+        return std::tie(n_rows, n_cols, nnz, pt, it, vt, use, codes, staged, long_rows, split) <
+               std::tie(o.n_rows, o.n_cols, o.nnz, o.pt, o.it, o.vt, o.use, o.codes, o.staged, o.long_rows, o.split);
     }
 };
 
@@ -75,6 +77,7 @@ struct spk_ctx_s {
 
 struct spk_plan_s {
     spk_ctx ctx = nullptr;
+    std::mutex mu;                       // one product's launches go out together (they share split and piece buffers)
     int kind = 0;                        // 0 = SpMV, 1 = solve
     CsrDev A{};
     spk_solver_cfg cfg{};
@@ -94,6 +97,7 @@ struct spk_plan_s {
     double *rt = nullptr, *u = nullptr, *v = nullptr, *uh = nullptr;   // CGS
     double *dinv = nullptr;              // Jacobi: 1 / diag(A)
     void *coo_rp = nullptr;              // COO SpMV: derived row pointer (owned)
+    void *split_buf = nullptr;           // split gathers (owned)
     void *long_buf = nullptr;            // long rows' pieces, their sums and each row's first piece (owned)
     void *codes_buf = nullptr;           // column codes: offset table + one byte per entry (owned)
     void *gm_V = nullptr, *gm_w = nullptr;   // GMRES basis and work vector (FP64, or FP32 in GMRES-IR)
@@ -228,8 +232,9 @@ bool stream_ok(const CsrDev &A) {
 // bpc <= 0: as many workgroups per CU as the occupancy calculator allows;
 // otherwise bpc per CU (extra workgroups queue until a slot frees).
 SpmvTune make_tune(spk_ctx ctx, const CsrDev &A, int kind, int lanes_log2, int remap, int nt, int pf, int bpc,
-                   int codes = 0, int pack = 0) {
+                   int codes = 0, int pack = 0, int split = 0) {
     SpmvTune t{kind, lanes_log2, 1, remap, nt, pf, 0};
+    t.split = kind == 0 && split && A.split.xg;
     t.cus = ctx->num_cu;
     t.codes = kind == 0 && codes && A.codes;
     t.pack = t.codes && pack && A.rowpack;
@@ -251,13 +256,37 @@ SpmvTune heuristic_tune(spk_ctx ctx, const CsrDev &A) {
     return make_tune(ctx, A, 1, l2, 1, 0, 0, 0);
 }
 
+// The column blocks (2^result columns) of a split of A's gathers, or -1 for
+// none.  vt: the value type of its products (FP32 vectors for all but F64).
+// An irregular pattern (no column codes) with tiles that mostly fit LDS (at
+// most 7.5 entries per row on average) and 32-bit stream positions.  Blocks of
+// 128 KB of the vector are gathered from LDS; when those would be more than
+// kSplitBlocks, blocks of 2^16 to 2^19 columns from L2.  Below 2^22 entries
+// plans keep the plain product, whose launch the allocation-free solve shares
+// (and the vector fits an XCD's 4 MB L2).  SPK_SPLIT=0 turns it off, 1 lifts
+// the size limits (tests).
+int split_shift(const CsrDev &A, int vt) {
+    const char *env = std::getenv("SPK_SPLIT");
+    if (env && std::strcmp(env, "0") == 0) return -1;
+    const bool forced = env && std::strcmp(env, "1") == 0;
+    if (A.codes || !stream_ok(A) || A.n_rows < 1 || A.n_cols < 1 || A.nnz < 1 || A.nnz > INT32_MAX) return -1;
+    if (!forced && (A.nnz > 7.5 * A.n_rows || A.nnz < (int64_t(1) << 22))) return -1;
+    for (int shift : {vt == SPK_F64 ? 14 : 15, 16, 17, 18, 19})
+        if (((A.n_cols - 1) >> shift) < spk::kSplitBlocks) return shift;
+    return -1;
+}
+
+TuneKey tune_key(const CsrDev &A, int use) {
+    return TuneKey{A.n_rows, A.n_cols, A.nnz, A.ptr_t, A.idx_t, A.val_t, use, A.codes != nullptr, stream_ok(A),
+                   A.max_row > spk::kLongRow, A.split.xg != nullptr || split_shift(A, A.val_t) >= 0};
+}
+
 // Times each candidate and keeps the fastest.  x, y: device vectors of the
 // plan's vector type (contents irrelevant for timing).  use = TUNE_CG times
 // the solvers' fused SpMV with st (stop flag clear) and partials.
 spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int use, SolveState *st,
                     double *partials, TuneResult *out, const void *fcg = nullptr) {
-    const TuneKey key{A.n_rows, A.n_cols, A.nnz, A.ptr_t, A.idx_t, A.val_t, use, A.codes != nullptr, stream_ok(A),
-                      A.max_row > spk::kLongRow};
+    const TuneKey key = tune_key(A, use);
     auto hit = ctx->tune_cache.find(key);
     if (hit != ctx->tune_cache.end()) {
         *out = hit->second;
@@ -327,6 +356,14 @@ spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int us
         // widens) resolve to the earlier candidate, so runs choose alike
         if (per < 0.97 * best.ms) best = TuneResult{t, per};
     }
+    if (A.split.xg) {
+        // the gathers ahead in column order, on the XCD-blocked tile order
+        // with streamed matrix loads (both launches are timed)
+        const SpmvTune c = make_tune(ctx, A, 0, 0, 64, 1, 1, 0, 0, 0, 1);
+        double per = 0.0;
+        SPK_HIP(ctx, time_one(c, &per));
+        if (per < 0.97 * best.ms) best = TuneResult{c, per};
+    }
     if (A.codes && best.tune.kind == 0) {
         // the best tile order and cache policy on one-byte column codes, with
         // packed row pointers (when built) and without, each at the coded
@@ -351,13 +388,14 @@ spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int us
 
 // SPK_SPMV_KERNEL forces a tiling (tests and sweeps use it): "stream" or
 // "vector:<lanes>", optionally followed by ",key=value" with keys remap, nt,
-// pf, bpc, codes, pack (e.g. "stream,pf=1,nt=1,remap=0,bpc=4,codes=0";
-// codes and pack default to 1 when the matrix has codes / packed rows).
+// pf, bpc, codes, pack, split (e.g. "stream,pf=1,nt=1,remap=0,bpc=4,codes=0";
+// codes and pack default to 1 when the matrix has codes / packed rows, split
+// to 0).
 bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
     const char *env = std::getenv("SPK_SPMV_KERNEL");
     if (!env || !*env) return false;
     std::string v(env);
-    int kind = -1, l2 = 0, remap = INT_MIN, nt = 0, pf = 1, bpc = 0, codes = 1, pack = 1;
+    int kind = -1, l2 = 0, remap = INT_MIN, nt = 0, pf = 1, bpc = 0, codes = 1, pack = 1, split = 0;
     size_t pos = 0;
     bool first = true;
     while (pos <= v.size()) {
@@ -384,6 +422,7 @@ bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
                 else if (k == "bpc") bpc = val;
                 else if (k == "codes") codes = val;
                 else if (k == "pack") pack = val;
+                else if (k == "split") split = val;
             }
         }
         pos = comma + 1;
@@ -391,7 +430,7 @@ bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
     if (kind < 0) return false;
     if (kind == 0 && !stream_ok(A)) kind = 1;
     if (remap < 0) remap = 1;   // unset (or negative): contiguous XCD eighths
-    *t = make_tune(ctx, A, kind, l2, remap, nt, pf, bpc, codes, pack);
+    *t = make_tune(ctx, A, kind, l2, remap, nt, pf, bpc, codes, pack, split);
     return true;
 }
 
@@ -487,6 +526,55 @@ spk_status build_codes(spk_plan pl) {
     if (h[2] == 0 && !(pack && std::strcmp(pack, "0") == 0))
         A.rowpack = static_cast<const char *>(A.codes) + spk::code_bytes(A.nnz);
     return SPK_OK;
+}
+
+// The split of A's gathers, where split_shift allows one and the tuner has not
+// already timed this shape and found it slower.  Without memory for it the products gather as they go.
+spk_status build_split(spk_plan pl, int use, int vt) {
+    spk_ctx ctx = pl->ctx;
+    CsrDev &A = pl->A;
+    const int shift = split_shift(A, vt);
+    if (shift < 0) return SPK_OK;
+    const char *forced = std::getenv("SPK_SPMV_KERNEL");
+    if (forced && *forced && !std::strstr(forced, "split=1")) return SPK_OK;
+    CsrDev probe = A;
+    probe.val_t = vt;
+    const auto hit = ctx->tune_cache.find(tune_key(probe, use));
+    if (hit != ctx->tune_cache.end() && !hit->second.tune.split) return SPK_OK;
+    const int blocks = static_cast<int>((A.n_cols - 1) >> shift) + 1;
+    void *buf = nullptr;
+    if (ctx->dpool.get(spk::split_buffer_bytes(A.n_rows, A.nnz, blocks), &buf) != hipSuccess) return SPK_OK;
+    spk::SplitDev d;
+    const uint32_t *count = nullptr;
+    unsigned *words = reinterpret_cast<unsigned *>(ctx->d_probe + spk::kCodeSlots);
+    unsigned h[3] = {0, 0, 0};
+    uint32_t total = 0;
+    if (hipMemsetAsync(words, 0, sizeof(h), ctx->stream) != hipSuccess ||
+        spk::launch_split_build(A, blocks, shift, buf, words, ctx->num_cu * 8, &d, &count, ctx->stream) != hipSuccess ||
+        hipMemcpyAsync(h, words, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipMemcpyAsync(&total, count, sizeof(total), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess) {
+        ctx->dpool.put(buf);
+        return fail(ctx, SPK_ERR_DEVICE, "split gathers");
+    }
+    if (h[2] != 0) {   // a tile of more than 65,535 entries
+        ctx->dpool.put(buf);
+        return SPK_OK;
+    }
+    d.count = total;
+    pl->split_buf = buf;
+    A.split = d;
+    return SPK_OK;
+}
+
+// The tuner kept the plain gathers: the split's memory goes back.
+void drop_split(spk_plan pl) {
+    if (pl->tune.split || !pl->split_buf) return;
+    (void)hipStreamSynchronize(pl->ctx->stream);
+    pl->ctx->dpool.put(pl->split_buf);
+    pl->split_buf = nullptr;
+    pl->A.split = spk::SplitDev{};
+    pl->A32.split = spk::SplitDev{};
 }
 
 // The pieces of the rows longer than kLongRow (k_long_pieces), for matrices
@@ -888,6 +976,8 @@ void release_workspace(spk_plan pl) {
     ctx->dpool.put(pl->dinv);
     ctx->dpool.put(pl->diag_flag);
     ctx->dpool.put(pl->coo_rp);
+    ctx->dpool.put(pl->split_buf);
+    pl->split_buf = nullptr;
     ctx->dpool.put(pl->long_buf);
     pl->long_buf = nullptr;
     ctx->dpool.put(pl->codes_buf);
@@ -1181,7 +1271,9 @@ static spk_status finish_spmv_plan(spk_ctx ctx, spk_plan pl, const spk_csr *A, s
     }
     s = build_codes(pl);
     if (s == SPK_OK) s = build_pieces(pl);
+    if (s == SPK_OK) s = build_split(pl, TUNE_PLAIN, A->val_type);
     if (s == SPK_OK) s = choose_tune(pl, x, y);
+    if (s == SPK_OK) drop_split(pl);
     (void)hipStreamSynchronize(ctx->stream);
     ctx->dpool.put(x);
     ctx->dpool.put(y);
@@ -1271,6 +1363,12 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         return cleanup(s, ctx->err);
     s = build_codes(pl);
     if (s == SPK_OK) s = build_pieces(pl);
+    if (s == SPK_OK && !fused_loop(cfg, n, regular))
+        s = build_split(pl, TUNE_CG,
+                        !mixed || A->val_type != SPK_F64           ? A->val_type
+                        : cfg.precision == SPK_PREC_MIXED_BF16 ? SPK_BF16
+                        : cfg.precision == SPK_PREC_MIXED_FP16 ? SPK_F16
+                                                               : SPK_F32);
     if (s != SPK_OK) return cleanup(s, ctx->err);
     const int64_t want = (n + int64_t(spk::kBlock) * 8 - 1) / (int64_t(spk::kBlock) * 8);
     // Streaming kernels: 4 workgroups per CU measured best for HBM copy rates.
@@ -1334,6 +1432,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
             s = choose_tune(pl, pl->p, pl->q, TUNE_CG, pl->st);
         }
         if (s != SPK_OK) return cleanup(s, ctx->err);
+        drop_split(pl);
     } else {
         if (!dget(nf, &pl->r32) || !dget(nf, &pl->p32) || !dget(nf, &pl->q32) || !dget(nf, &pl->d32) ||
             !dget(sizeof(SolveState), &pl->st_in) || !hget(sizeof(SolveState), &pl->h_st_in) ||
@@ -1383,8 +1482,9 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         }
         pl->A = outer;
         if (s != SPK_OK) return cleanup(s, ctx->err);
+        drop_split(pl);
         pl->tune32 = pl->tune;
-        pl->tune = heuristic_tune(ctx, pl->A);
+        pl->tune = pl->A.split.xg ? make_tune(ctx, pl->A, 0, 0, 64, 1, 1, 0, 0, 0, 1) : heuristic_tune(ctx, pl->A);
     }
     if (resident && resident_shape(pl, res_rows, max_chunk, mixed)) {
         const size_t cb = kResidentCtlBytes;
@@ -1450,7 +1550,10 @@ spk_status spk_execute_spmv(spk_plan pl, const void *x, void *y) {
     hipEvent_t e = nullptr;
     spk_status s = prof_begin(pl, &e);
     if (s != SPK_OK) return s;
-    SPK_HIP(ctx, spk::launch_spmv(pl->A, pl->tune, x, y, ctx->stream));
+    {
+        std::lock_guard<std::mutex> lk(pl->mu);
+        SPK_HIP(ctx, spk::launch_spmv(pl->A, pl->tune, x, y, ctx->stream));
+    }
     s = prof_end(pl, e);
     if (s != SPK_OK) return s;
     SPK_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -1909,9 +2012,7 @@ spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg
     pl.vec_grid = static_cast<int>(std::clamp<int64_t>(want, 1, int64_t(ctx->num_cu) * 4));
     // the launch shape an earlier plan of this shape tuned (read from the
     // context's cache, never added to it), else the heuristic one
-    const TuneKey key{pl.A.n_rows, pl.A.n_cols, pl.A.nnz, pl.A.ptr_t, pl.A.idx_t, pl.A.val_t,
-                      pl.fused ? TUNE_FCG : TUNE_CG, false,
-                      stream_ok(pl.A), pl.A.max_row > spk::kLongRow};
+    const TuneKey key = tune_key(pl.A, pl.fused ? TUNE_FCG : TUNE_CG);
     if (!forced_tune(ctx, pl.A, &pl.tune)) {
         auto hit = ctx->tune_cache.find(key);
         pl.tune = hit != ctx->tune_cache.end() && pl.A.nnz >= 100000 ? hit->second.tune : heuristic_tune(ctx, pl.A);

@@ -323,6 +323,12 @@ struct PlainGather {   // x[c]
     __device__ __forceinline__ C operator()(int64_t c) const { return static_cast<C>(x[c]); }
 };
 
+template <typename X, typename C>
+struct LdsGather {   // x[c], x in LDS
+    const X *x;
+    __device__ __forceinline__ C operator()(int64_t c) const { return static_cast<C>(x[c]); }
+};
+
 template <typename T>
 struct PUpdateGather {   // p_k[c] = fma(beta, p_{k-1}[c], r_k[c]): the CG direction formed on the fly
     T beta;

@@ -151,8 +151,28 @@ struct SpmvTune {
     int bpc;         // workgroups per CU the grid was sized for
     int codes = 0;   // LDS tiles: 1 = read the matrix's one-byte column codes (CsrDev::codes)
     int pack = 0;    // with codes: 1 = read the packed row pointers (CsrDev::rowpack)
+    int split = 0;   // LDS tiles: 1 = the gathers run ahead in column order (CsrDev::split)
     int cus = 0;     // compute units of the device (0 = unknown: every workgroup walks tiles)
 };
+
+// The gathers of an irregular product, taken in an order of their own.  The
+// entries of the row tiles (those of at most kStreamCap entries) are listed by
+// column block (2^shift columns), within a block by tile: the stream.  A first
+// launch reads x[cols[j]] for every stream position j into xg[j], a block's
+// slice of x at a time; the row tiles then read their segments of xg (one per
+// block) and pick entry k's value at place perm[k] of them.
+struct SplitDev {
+    void *xg = nullptr;              // one value of x per stream position (8 bytes each)
+    const int32_t *cols = nullptr;   // stream position -> column
+    const uint16_t *perm = nullptr;  // entry -> place in its tile's segments
+    const uint32_t *seg = nullptr;   // [tile][block]: the segment's first stream position
+    const uint16_t *off = nullptr;   // [tile][block], blocks + 1 each: its first place
+    const void *rows = nullptr;      // packed row pointers (as CsrDev::rowpack)
+    int64_t count = 0;               // stream positions
+    int blocks = 0, shift = 0;
+};
+
+constexpr int kSplitBlocks = 128;    // most column blocks (two per lane of a wave)
 
 // Device CSR view with runtime-typed arrays.
 struct CsrDev {
@@ -179,6 +199,8 @@ struct CsrDev {
     int n_pieces = 0;
     const int32_t *long_base = nullptr;
     double *piece_sums = nullptr;
+    // Optional split of the gathers (xg null when absent): see SplitDev.
+    SplitDev split;
 };
 
 constexpr int kLongRow = 256;   // rows longer than this are summed by whole workgroups
@@ -198,10 +220,13 @@ constexpr int kCodeSlots = 1024;  // plan-time hash table of distinct offsets (p
 // Byte sizes of the plan's code buffer: the offset table, the codes (rounded
 // to 16 bytes), then the packed row pointers (tiles + 1 int64, n uint16).
 inline size_t code_bytes(int64_t nnz) { return (static_cast<size_t>(nnz) + 15) & ~size_t(15); }
-inline size_t code_buffer_bytes(int64_t n_rows, int64_t nnz) {
+// Bytes of the packed row pointers of n rows: tiles + 1 int64, n uint16.
+inline size_t rowpack_bytes(int64_t n_rows) {
     const size_t tiles = static_cast<size_t>((n_rows + kTileRows - 1) / kTileRows);
-    return sizeof(int64_t) * kCodeDict + code_bytes(nnz) + sizeof(int64_t) * (tiles + 1) +
-           ((sizeof(uint16_t) * static_cast<size_t>(n_rows) + 15) & ~size_t(15));
+    return sizeof(int64_t) * (tiles + 1) + ((sizeof(uint16_t) * static_cast<size_t>(n_rows) + 15) & ~size_t(15));
+}
+inline size_t code_buffer_bytes(int64_t n_rows, int64_t nnz) {
+    return sizeof(int64_t) * kCodeDict + code_bytes(nnz) + rowpack_bytes(n_rows);
 }
 
 // Validation flag bits (set by the GPU check, order resolved on the host).

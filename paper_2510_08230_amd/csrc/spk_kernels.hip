@@ -1006,6 +1006,18 @@ hipError_t launch_code_build(const CsrDev &A, int step, long long *table, unsign
     });
 }
 
+hipError_t launch_rowpack(const CsrDev &A, void *rows, unsigned *words, int grid, hipStream_t s) {
+    int64_t *tb = static_cast<int64_t *>(rows);
+    uint16_t *ro = reinterpret_cast<uint16_t *>(tb + (A.n_rows + kTileRows - 1) / kTileRows + 1);
+    if (A.ptr_t == 0)
+        hipLaunchKernelGGL((k_rowpack<int32_t>), dim3(grid), dim3(kBlock), 0, s, A.n_rows,
+                           static_cast<const int32_t *>(A.rp), tb, ro, words);
+    else
+        hipLaunchKernelGGL((k_rowpack<int64_t>), dim3(grid), dim3(kBlock), 0, s, A.n_rows,
+                           static_cast<const int64_t *>(A.rp), tb, ro, words);
+    return hipGetLastError();
+}
+
 hipError_t launch_coo_validate(int64_t n_rows, int64_t n_cols, int64_t nnz, const void *row, const void *col,
                                int idx_t, unsigned *flags, int max_grid, hipStream_t s) {
     if (nnz == 0) return hipSuccess;
@@ -1259,7 +1271,15 @@ int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t) {
         if (lr) q(with);
         else q(without);
     };
-    if (t.kind == 0 && t.codes && A.codes) {   // the coded instances the launch will use
+    if (t.kind == 0 && t.split && A.split.xg) {
+        if (A.val_t == 0) {
+            q(k_spmv_split<double, double, double, EpiPq<double>>);
+            q(k_spmv_split<double, double, double, EpiPlain<double>>);
+        } else {
+            q(k_spmv_split<float, float, float, EpiPq<float>>);
+            q(k_spmv_split<float, float, float, EpiPlain<float>>);
+        }
+    } else if (t.kind == 0 && t.codes && A.codes) {   // the coded instances the launch will use
         const bool pack = t.pack && A.rowpack;
         if (A.val_t == 0) {
             if (pack) {

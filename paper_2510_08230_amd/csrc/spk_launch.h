@@ -36,6 +36,16 @@ hipError_t launch_pattern_probe(const CsrDev &A, int step, long long *table, uns
 // codes_base holds code_buffer_bytes(n_rows, nnz) bytes.
 hipError_t launch_code_build(const CsrDev &A, int step, long long *table, unsigned *words, void *codes_base,
                              int grid, hipStream_t s);
+// Packed row pointers (rowpack_bytes(n_rows)) on their own: words[1] must be 0;
+// words[2] is set when a row offset within its tile exceeds 65535.
+hipError_t launch_rowpack(const CsrDev &A, void *rows, unsigned *words, int grid, hipStream_t s);
+// Split gathers (plan time, spk_split.hip): blocks of 2^shift columns cover
+// n_cols; buf holds split_buffer_bytes.  *out describes the structure except
+// its count, which *count points to on the device; words as for
+// launch_rowpack.
+size_t split_buffer_bytes(int64_t n_rows, int64_t nnz, int blocks);
+hipError_t launch_split_build(const CsrDev &A, int blocks, int shift, void *buf, unsigned *words, int grid, SplitDev *out,
+                              const uint32_t **count, hipStream_t s);
 // COO (idx_t 0 = int32, 1 = int64): flags gets VFLAG_BAD_FIRST for a row
 // index out of range, VFLAG_BAD_COLUMN, VFLAG_UNSORTED for a decreasing row.
 hipError_t launch_coo_validate(int64_t n_rows, int64_t n_cols, int64_t nnz, const void *row, const void *col,

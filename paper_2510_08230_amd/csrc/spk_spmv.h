@@ -356,6 +356,201 @@ __global__ __launch_bounds__(kBlock) void k_spmv_vector(int64_t n, const P *__re
     epi.finish();
 }
 
+// ---- split gathers (SplitDev) ----------------------------------------------------
+// A random pattern's product is bound by the lines its gathers fill: at 1e7
+// columns nearly every 8-byte read brings a 128-byte line through the fabric
+// (8.4 GB per product of 7e7 entries), at 1e6 from the L2 (170e9 reads/s).
+// Taken block by block of 2^shift columns, the gathers find their slice of x
+// in LDS (blocks of 128 KB) or in the XCD's L2 (larger ones); what is added
+// is streamed: 4 bytes of column and 8 of value per entry out of the first
+// launch, 8 of value and 2 of place into the second.  Row sums run in storage
+// order on the caller's values, so products equal the plain ones bit for bit.
+// Random pattern, 7 entries per row, us per product, plain / split (the two
+// launches): FP64 n = 1e6 68 / 52 (20 + 32), n = 2e6 180 / 110, n = 1e7
+// 1,170 / 772 (474 + 322 under the profiler; the L2 gathers are bound by the
+// misses a CU keeps in flight); FP32 n = 3e6 228 / 119 (35 + 84).
+constexpr int kSplitDepth = 8;   // gathers in flight per thread
+
+template <typename X, class Epi>
+__global__ __launch_bounds__(kBlock) void k_split_gather(const int32_t *__restrict__ cols, int64_t count,
+                                                         const X *__restrict__ x, X *__restrict__ xg, Epi epi) {
+    if (epi.skip()) return;
+    // each XCD walks its own eighth of the stream, so the slices of x that its
+    // L2 holds are its own
+    const int64_t span = static_cast<int64_t>(kBlock) * kSplitDepth;
+    for (TileIter it((count + span - 1) / span, 1); it.valid(); it.next()) {
+        const int64_t base = it.tile() * span + threadIdx.x;
+        int32_t c[kSplitDepth];
+        X v[kSplitDepth];
+#pragma unroll
+        for (int u = 0; u < kSplitDepth; ++u) {
+            const int64_t j = base + u * kBlock;
+            c[u] = __builtin_nontemporal_load(cols + (j < count ? j : count - 1));
+        }
+#pragma unroll
+        for (int u = 0; u < kSplitDepth; ++u) v[u] = x[c[u]];
+#pragma unroll
+        for (int u = 0; u < kSplitDepth; ++u) {
+            const int64_t j = base + u * kBlock;
+            if (j < count) __builtin_nontemporal_store(v[u], xg + j);
+        }
+    }
+}
+
+// The same with the block's slice of x in LDS: a workgroup loads it and takes
+// its part (of `parts`) of the block's stream.  start[c]: block c's first
+// stream position (seg of tile 0).
+constexpr int kSplitLdsThreads = 1024;
+constexpr size_t kSplitLds = size_t(128) << 10;
+
+template <typename X, class Epi>
+__global__ __launch_bounds__(kSplitLdsThreads) void k_split_gather_lds(SplitDev sp, int parts, int64_t n_cols,
+                                                                       const X *__restrict__ x, Epi epi) {
+    if (epi.skip()) return;
+    __shared__ X lx[kSplitLds / sizeof(X)];
+    const int c = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int64_t first = static_cast<int64_t>(c) << sp.shift;
+    const int width = static_cast<int>(min(n_cols - first, static_cast<int64_t>(1) << sp.shift));
+    const int64_t b0 = sp.seg[c], b1 = c + 1 < sp.blocks ? static_cast<int64_t>(sp.seg[c + 1]) : sp.count;
+    const int64_t j0 = b0 + (b1 - b0) * part / parts, j1 = b0 + (b1 - b0) * (part + 1) / parts;
+    const X *xs = x + first;
+    constexpr int U = 8;
+    for (int i = threadIdx.x; i < width; i += U * kSplitLdsThreads) {
+        X v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = xs[i + u * kSplitLdsThreads < width ? i + u * kSplitLdsThreads : i];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * kSplitLdsThreads < width) lx[i + u * kSplitLdsThreads] = v[u];
+    }
+    __syncthreads();
+    X *xg = static_cast<X *>(sp.xg);
+    for (int64_t base = j0 + threadIdx.x; base < j1; base += U * kSplitLdsThreads) {
+        int32_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t j = base + u * kSplitLdsThreads;
+            k[u] = sp.cols[j < j1 ? j : j1 - 1] - static_cast<int32_t>(first);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t j = base + u * kSplitLdsThreads;
+            if (j < j1) xg[j] = lx[k[u]];
+        }
+    }
+}
+
+// One tile's segment table, up to two blocks per lane.
+struct SplitMeta {
+    uint32_t seg[2];
+    uint16_t a[2], b[2];
+    __device__ __forceinline__ void load(const SplitDev &sp, int64_t tile) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i = (threadIdx.x & 63) + 64 * h;
+            const int c = i < sp.blocks ? i : sp.blocks - 1;
+            seg[h] = sp.seg[tile * sp.blocks + c];
+            const uint16_t *o = sp.off + tile * (sp.blocks + 1) + c;
+            a[h] = o[0];
+            b[h] = o[1];
+        }
+    }
+};
+
+// The row tiles of a product whose gathers have run.  Tiles of more than
+// kStreamCap entries gather from x themselves (ci: the plain indices, 64-bit
+// ones when ci64).
+template <typename V, typename X, typename C, class Epi>
+__global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, const void *__restrict__ ci, int ci64,
+                                                       const V *__restrict__ va, const X *__restrict__ x, SplitDev sp,
+                                                       int remap, int nt, int walkers, Epi epi_in, LongArg<2> lra) {
+    Epi epi = epi_in;
+    if (epi.skip()) return;
+    const uint32_t W = walkers > 0 && static_cast<uint32_t>(walkers) < gridDim.x ? walkers : gridDim.x;
+    if (blockIdx.x >= W) {   // uniform
+        epi.finish();
+        return;
+    }
+    __shared__ u32x4 lv[Chunks<V>::LDS];
+    __shared__ u32x4 lp[Chunks<uint16_t>::LDS];
+    __shared__ X lx[kStreamCap];
+    const RowPack *rp = static_cast<const RowPack *>(sp.rows);
+    const X *xg = static_cast<const X *>(sp.xg);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t T = (n + kTileRows - 1) / kTileRows;
+    TileIter it(T, remap, W);
+    if (it.valid()) {
+        TileMeta<RowPack> cur, nxt;
+        SplitMeta sc, sn;
+        cur.load(rp, n, it.tile());
+        sc.load(sp, it.tile());
+        while (true) {
+            TileIter after = it;
+            after.next();
+            const bool more = after.valid();
+            const int64_t r1 = min(cur.r0 + static_cast<int64_t>(kTileRows), n);
+            const int64_t row = cur.r0 + threadIdx.x;
+            const int64_t s = cur.first(), e = cur.end();
+            const int64_t a = cur.lo(), b = cur.hi();
+            if (e - s <= kStreamCap) {
+                dma_chunks<V>(va, s, e, nnz, lv, nt);
+                dma_chunks<uint16_t>(sp.perm, s, e, nnz, lp, nt);
+                // the segments, a wave each in turn, 4 bytes per lane
+                auto segment = [&](uint32_t g, int at, int end) {
+                    const int words = (end - at) * static_cast<int>(sizeof(X) / 4);
+                    const uint32_t *src = reinterpret_cast<const uint32_t *>(xg + g);
+                    uint32_t *dst = reinterpret_cast<uint32_t *>(lx + at);
+                    for (int q = 0; q < words; q += 64)
+                        if (q + lane < words)
+                            __builtin_amdgcn_global_load_lds(static_cast<const void *>(src + q + lane),
+                                                             (lds_void *)(dst + q), 4, 0, 0);
+                };
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    for (int c = wid; c < min(64, sp.blocks - 64 * h); c += kBlock / 64)
+                        segment(__builtin_amdgcn_readlane(sc.seg[h], c), __builtin_amdgcn_readlane(static_cast<int>(sc.a[h]), c),
+                                __builtin_amdgcn_readlane(static_cast<int>(sc.b[h]), c));
+                if (more) {
+                    nxt.load(rp, n, after.tile());
+                    sn.load(sp, after.tile());
+                }
+                const auto pv = pre_of(epi, row < r1 ? row : r1 - 1);
+                __builtin_amdgcn_s_waitcnt(0);   // this wave's DMA has landed
+                __syncthreads();                 // ... and every other wave's
+                __builtin_amdgcn_s_setprio(2);   // (as in spmv_tiles_lds)
+                if (row < r1)
+                    emit_row(epi, row,
+                             row_from_lds<V, uint16_t, C>(reinterpret_cast<const V *>(lv),
+                                                          reinterpret_cast<const uint16_t *>(lp), a, b,
+                                                          s & ~static_cast<int64_t>(Chunks<V>::EPC - 1),
+                                                          s & ~static_cast<int64_t>(Chunks<uint16_t>::EPC - 1),
+                                                          LdsGather<X, C>{lx}),
+                             pv);
+                __builtin_amdgcn_s_setprio(0);
+                lds_barrier();
+            } else {
+                if (more) {
+                    nxt.load(rp, n, after.tile());
+                    sn.load(sp, after.tile());
+                }
+                const PlainGather<X, C> gx{x};
+                if (row < r1 && lra.base && b - a > kLongRow)   // its pieces have been summed
+                    epi.row(row, lra.template sum<C>(row, b - a));
+                else if (row < r1)
+                    epi.row(row, ci64 ? row_from_global<V, int64_t, C, kRowUnroll>(va, static_cast<const int64_t *>(ci), a,
+                                                                                   b, gx, nt)
+                                      : row_from_global<V, int32_t, C, kRowUnroll>(va, static_cast<const int32_t *>(ci), a,
+                                                                                   b, gx, nt));
+            }
+            if (!more) break;
+            it = after;
+            cur = nxt;
+            sc = sn;
+        }
+    }
+    epi.finish();
+}
+
 template <class F>
 hipError_t dispatch_idx(const CsrDev &A, F &&f) {
     if (A.ptr_t == 0) {
@@ -383,6 +578,33 @@ int resident_per_cu() {
 template <typename V, typename X, typename C, class Epi>
 hipError_t launch_family(const CsrDev &A, const SpmvTune &t, const X *x, const Epi &epi, hipStream_t s) {
     if (A.n_rows == 0) return hipSuccess;
+    if constexpr (!HasGather<Epi>::value) {
+        if (t.kind == 0 && t.split && A.split.xg && (reinterpret_cast<uintptr_t>(A.va) & 15) == 0) {
+            constexpr auto K = k_spmv_split<V, X, C, Epi>;
+            const int per_cu = resident_per_cu<K>();
+            const int walk = t.cus > 0 && per_cu > 0 ? std::min(t.grid, t.cus * per_cu) : 0;
+            if (A.pieces) {
+                auto pieces = [&](auto ci) {
+                    hipLaunchKernelGGL((k_long_pieces<V, pointee_t<decltype(ci)>, X, C, Epi>),
+                                       dim3(std::min(A.n_pieces, kMaxGrid)), dim3(kBlock), 0, s, A.pieces, A.n_pieces, ci,
+                                       static_cast<const V *>(A.va), x, t.nt, A.piece_sums, epi);
+                };
+                if (A.idx_t == 0) pieces(static_cast<const int32_t *>(A.ci));
+                else pieces(static_cast<const int64_t *>(A.ci));
+            }
+            if (A.split.count > 0 && (sizeof(X) << A.split.shift) <= kSplitLds)
+                hipLaunchKernelGGL((k_split_gather_lds<X, Epi>),
+                                   dim3(A.split.blocks * std::max(1, t.cus / A.split.blocks)), dim3(kSplitLdsThreads), 0, s,
+                                   A.split, std::max(1, t.cus / A.split.blocks), A.n_cols, x, epi);
+            else if (A.split.count > 0)
+                hipLaunchKernelGGL((k_split_gather<X, Epi>), dim3(t.cus > 0 ? std::min(t.cus * 8, kMaxGrid) : t.grid),
+                                   dim3(kBlock), 0, s, A.split.cols, A.split.count, x, static_cast<X *>(A.split.xg), epi);
+            hipLaunchKernelGGL(K, dim3(t.grid), dim3(kBlock), 0, s, A.n_rows, A.nnz, A.ci, A.idx_t, static_cast<const V *>(A.va),
+                               x, A.split, t.xcd_remap, t.nt, walk, epi,
+                               LongArg<2>{A.pieces ? A.long_base : nullptr, A.piece_sums});
+            return hipGetLastError();
+        }
+    }
     // tile walkers of a row-tile kernel: the grid, or as many workgroups as
     // that kernel holds resident on the device if fewer
     auto walkers = [&](int per_cu) { return t.cus > 0 && per_cu > 0 ? std::min(t.grid, t.cus * per_cu) : 0; };
