@@ -138,9 +138,10 @@ def index_bytes(info, n, nnz, sp):
     """Index bytes one row-tile product reads: the column index (or, with
     column codes, one byte per entry plus the 2 KiB offset table) and the row
     pointers (or, when packed, an int64 per 256-row tile and a uint16 per
-    row).  sp: row-pointer width of the caller's CSR."""
+    row; with row patterns one byte per row plus the 5 KiB pattern table in
+    place of the entries' bytes).  sp: row-pointer width of the caller's CSR."""
     cc = int(info.get("col_codes") or 0)
-    cols = nnz * 1 + 2048 if cc & 1 else nnz * 4
+    cols = n + 5120 if cc & 4 else nnz * 1 + 2048 if cc & 1 else nnz * 4
     rows = ((n + 255) // 256 + 1) * 8 + 2 * n if cc & 2 else (n + 1) * sp
     return cols + rows
 

@@ -178,7 +178,10 @@ typedef struct {
                                   its column offset from the row in a table of at most 256
                                   offsets derived at plan time, in place of col_idx;
                                   bit 1: it also reads packed row pointers (an int64 per
-                                  256-row tile, a uint16 offset per row) in place of row_ptr */
+                                  256-row tile, a uint16 offset per row) in place of row_ptr;
+                                  bit 2: with both, it reads one byte per row naming the row's
+                                  whole sequence of offsets in a table of at most 256 distinct
+                                  rows, in place of the entries' bytes */
     double spmv_ms;            /* measured time of the chosen SpMV (0 if not tuned) */
     int32_t fused_loop;        /* 1 = CG runs one launch per iteration: the SpMV step also forms
                                   the direction from the previous r, q and p at every gathered

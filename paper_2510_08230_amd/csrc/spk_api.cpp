@@ -97,6 +97,7 @@ struct spk_plan_s {
     double *rt = nullptr, *u = nullptr, *v = nullptr, *uh = nullptr;   // CGS
     double *dinv = nullptr;              // Jacobi: 1 / diag(A)
     void *coo_rp = nullptr;              // COO SpMV: derived row pointer (owned)
+    void *pat_buf = nullptr;             // row patterns (owned)
     void *split_buf = nullptr;           // split gathers (owned)
     void *long_buf = nullptr;            // long rows' pieces, their sums and each row's first piece (owned)
     void *codes_buf = nullptr;           // column codes: offset table + one byte per entry (owned)
@@ -232,12 +233,13 @@ bool stream_ok(const CsrDev &A) {
 // bpc <= 0: as many workgroups per CU as the occupancy calculator allows;
 // otherwise bpc per CU (extra workgroups queue until a slot frees).
 SpmvTune make_tune(spk_ctx ctx, const CsrDev &A, int kind, int lanes_log2, int remap, int nt, int pf, int bpc,
-                   int codes = 0, int pack = 0, int split = 0) {
+                   int codes = 0, int pack = 0, int split = 0, int pats = 0) {
     SpmvTune t{kind, lanes_log2, 1, remap, nt, pf, 0};
     t.split = kind == 0 && split && A.split.xg;
     t.cus = ctx->num_cu;
     t.codes = kind == 0 && codes && A.codes;
     t.pack = t.codes && pack && A.rowpack;
+    t.pats = t.pack && pats && A.patterns;
     const int occ = spk::spmv_blocks_per_cu(A, t);
     const int use = (bpc <= 0) ? occ : std::min(bpc, 32);   // a forced count may oversubscribe
     t.bpc = use;
@@ -250,7 +252,7 @@ SpmvTune make_tune(spk_ctx ctx, const CsrDev &A, int kind, int lanes_log2, int r
 
 SpmvTune heuristic_tune(spk_ctx ctx, const CsrDev &A) {
     const double mean = A.n_rows > 0 ? static_cast<double>(A.nnz) / A.n_rows : 0.0;
-    if (mean <= 16.0 && stream_ok(A)) return make_tune(ctx, A, 0, 0, 0, 0, 1, 0, 1, 1);
+    if (mean <= 16.0 && stream_ok(A)) return make_tune(ctx, A, 0, 0, 0, 0, 1, 0, 1, 1, 0, 1);
     int l2 = 0;
     while ((1 << l2) < mean && l2 < 6) ++l2;
     return make_tune(ctx, A, 1, l2, 1, 0, 0, 0);
@@ -380,6 +382,12 @@ spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int us
             if (per < 0.97 * coded.ms) coded = TuneResult{c, per};
         }
         if (!(best.ms < 0.97 * coded.ms)) best = coded;
+        if (A.patterns) {   // fewer bytes still: kept when no slower
+            const SpmvTune c = make_tune(ctx, A, 0, 0, b.xcd_remap, b.nt, b.pf, 0, 1, 1, 0, 1);
+            double per = 0.0;
+            SPK_HIP(ctx, time_one(c, &per));
+            if (per <= best.ms) best = TuneResult{c, per};
+        }
     }
     ctx->tune_cache[key] = best;
     *out = best;
@@ -388,14 +396,14 @@ spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int us
 
 // SPK_SPMV_KERNEL forces a tiling (tests and sweeps use it): "stream" or
 // "vector:<lanes>", optionally followed by ",key=value" with keys remap, nt,
-// pf, bpc, codes, pack, split (e.g. "stream,pf=1,nt=1,remap=0,bpc=4,codes=0";
+// pf, bpc, codes, pack, split, pats (e.g. "stream,pf=1,nt=1,remap=0,bpc=4,codes=0";
 // codes and pack default to 1 when the matrix has codes / packed rows, split
-// to 0).
+// and pats to 0).
 bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
     const char *env = std::getenv("SPK_SPMV_KERNEL");
     if (!env || !*env) return false;
     std::string v(env);
-    int kind = -1, l2 = 0, remap = INT_MIN, nt = 0, pf = 1, bpc = 0, codes = 1, pack = 1, split = 0;
+    int kind = -1, l2 = 0, remap = INT_MIN, nt = 0, pf = 1, bpc = 0, codes = 1, pack = 1, split = 0, pats = 0;
     size_t pos = 0;
     bool first = true;
     while (pos <= v.size()) {
@@ -423,6 +431,7 @@ bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
                 else if (k == "codes") codes = val;
                 else if (k == "pack") pack = val;
                 else if (k == "split") split = val;
+                else if (k == "pats") pats = val;
             }
         }
         pos = comma + 1;
@@ -430,7 +439,7 @@ bool forced_tune(spk_ctx ctx, const CsrDev &A, SpmvTune *t) {
     if (kind < 0) return false;
     if (kind == 0 && !stream_ok(A)) kind = 1;
     if (remap < 0) remap = 1;   // unset (or negative): contiguous XCD eighths
-    *t = make_tune(ctx, A, kind, l2, remap, nt, pf, bpc, codes, pack, split);
+    *t = make_tune(ctx, A, kind, l2, remap, nt, pf, bpc, codes, pack, split, pats);
     return true;
 }
 
@@ -462,7 +471,9 @@ spk_status choose_tune(spk_plan pl, const void *x, void *y, int use = TUNE_PLAIN
     pl->info.xcd_remap = pl->tune.xcd_remap;
     pl->info.nontemporal = pl->tune.nt;
     pl->info.col_codes =
-        (pl->tune.kind == 0 && pl->tune.codes && A.codes) ? ((pl->tune.pack && A.rowpack) ? 3 : 1) : 0;
+        (pl->tune.kind == 0 && pl->tune.codes && A.codes)
+            ? ((pl->tune.pack && A.rowpack) ? ((pl->tune.pats && A.patterns) ? 7 : 3) : 1)
+            : 0;
     return SPK_OK;
 }
 
@@ -525,6 +536,30 @@ spk_status build_codes(spk_plan pl) {
     const char *pack = std::getenv("SPK_ROW_PACK");
     if (h[2] == 0 && !(pack && std::strcmp(pack, "0") == 0))
         A.rowpack = static_cast<const char *>(A.codes) + spk::code_bytes(A.nnz);
+    return SPK_OK;
+}
+
+// Row patterns of a coded matrix with packed row pointers (k_pat_*): a byte
+// per row when its rows hold at most kPatterns distinct offset sequences.
+// SPK_ROW_PATTERNS=0 turns them off.  Without them the codes stay in use.
+spk_status build_patterns(spk_plan pl) {
+    spk_ctx ctx = pl->ctx;
+    CsrDev &A = pl->A;
+    const char *env = std::getenv("SPK_ROW_PATTERNS");
+    if (!A.codes || !A.rowpack || A.max_row > spk::kPatternRow || (env && std::strcmp(env, "0") == 0)) return SPK_OK;
+    void *buf = nullptr;
+    if (ctx->dpool.get(spk::pattern_buffer_bytes(A.n_rows), &buf) != hipSuccess) return SPK_OK;
+    unsigned *words = reinterpret_cast<unsigned *>(ctx->d_probe + spk::kCodeSlots);
+    unsigned h[2] = {0, 0};
+    const bool ok = spk::launch_pattern_build(A, words, buf, ctx->num_cu * 8, ctx->stream) == hipSuccess &&
+                    hipMemcpyAsync(h, words, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) == hipSuccess &&
+                    hipStreamSynchronize(ctx->stream) == hipSuccess;
+    if (!ok || h[1] != 0) {
+        ctx->dpool.put(buf);
+        return ok ? SPK_OK : fail(ctx, SPK_ERR_DEVICE, "row patterns");
+    }
+    pl->pat_buf = buf;
+    A.patterns = spk::pattern_bytes(buf);
     return SPK_OK;
 }
 
@@ -976,6 +1011,8 @@ void release_workspace(spk_plan pl) {
     ctx->dpool.put(pl->dinv);
     ctx->dpool.put(pl->diag_flag);
     ctx->dpool.put(pl->coo_rp);
+    ctx->dpool.put(pl->pat_buf);
+    pl->pat_buf = nullptr;
     ctx->dpool.put(pl->split_buf);
     pl->split_buf = nullptr;
     ctx->dpool.put(pl->long_buf);
@@ -1270,6 +1307,7 @@ static spk_status finish_spmv_plan(spk_ctx ctx, spk_plan pl, const spk_csr *A, s
         (void)hipMemsetAsync(x, 0, A->n_cols * vb, ctx->stream);
     }
     s = build_codes(pl);
+    if (s == SPK_OK) s = build_patterns(pl);
     if (s == SPK_OK) s = build_pieces(pl);
     if (s == SPK_OK) s = build_split(pl, TUNE_PLAIN, A->val_type);
     if (s == SPK_OK) s = choose_tune(pl, x, y);
@@ -1362,6 +1400,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
     if (fused_needs_pattern(cfg, n) && (s = pattern_regular(ctx, pl->A, &regular)) != SPK_OK)
         return cleanup(s, ctx->err);
     s = build_codes(pl);
+    if (s == SPK_OK) s = build_patterns(pl);
     if (s == SPK_OK) s = build_pieces(pl);
     if (s == SPK_OK && !fused_loop(cfg, n, regular))
         s = build_split(pl, TUNE_CG,

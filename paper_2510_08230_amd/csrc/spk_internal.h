@@ -151,6 +151,7 @@ struct SpmvTune {
     int bpc;         // workgroups per CU the grid was sized for
     int codes = 0;   // LDS tiles: 1 = read the matrix's one-byte column codes (CsrDev::codes)
     int pack = 0;    // with codes: 1 = read the packed row pointers (CsrDev::rowpack)
+    int pats = 0;    // LDS tiles: 1 = read the matrix's row patterns (CsrDev::patterns)
     int split = 0;   // LDS tiles: 1 = the gathers run ahead in column order (CsrDev::split)
     int cus = 0;     // compute units of the device (0 = unknown: every workgroup walks tiles)
 };
@@ -187,6 +188,10 @@ struct CsrDev {
     // int64 first entry of every 256-row tile (tiles + 1 values), followed
     // directly by one uint16 per row, its first entry less its tile's.
     const void *rowpack = nullptr;
+    // Optional row patterns (null when absent; only with codes and rowpack):
+    // byte i names row i's whole sequence of column offsets in the pattern
+    // table (RowPatterns) stored just before the bytes.
+    const void *patterns = nullptr;
     // The longest row's entry count (measured when the plan validates A; 0 =
     // unknown).  Above kLongRow the row tiles sum such rows with the whole
     // workgroup (host side only: it sets the kernels' long-row argument).
@@ -212,6 +217,15 @@ struct LongPiece {
     int64_t first;   // entry
     int32_t len;
     int32_t row;
+};
+
+// The distinct rows of a coded matrix, as sequences of column offsets c - i.
+constexpr int kPatterns = 256;      // distinct rows
+constexpr int kPatternOffs = 1024;  // offsets of all of them together
+constexpr int kPatternRow = 64;     // longest row
+struct RowPatterns {
+    uint32_t info[kPatterns];       // first offset | entries << 16
+    int32_t offs[kPatternOffs];
 };
 
 constexpr int kCodeDict = 256;    // distinct column offsets a code table holds

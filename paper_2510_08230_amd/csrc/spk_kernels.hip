@@ -832,6 +832,178 @@ __global__ __launch_bounds__(kBlock) void k_rowpack(int64_t n_rows, const P *__r
     if (bad) atomicOr(&words[2], 1u);
 }
 
+// Row patterns, from a coded matrix (codes, offset table and packed row
+// pointers built).  A row's key is its code sequence: up to kPatExact codes
+// themselves and their count, longer rows a hash.
+//   k_pat_scan: every row claims or finds its key's slot in a table of
+//     kPatterns keys and stores the slot; a slot's claimant leaves its row.
+//     Each workgroup keeps the slots it has seen in LDS.
+//   k_pat_table: one workgroup, a thread per slot: the slots' offsets from
+//     their rows.
+//   k_pat_verify (rows longer than kPatExact): every row's offsets against its
+//     pattern's, entry by entry.
+// words[1] != 0: no patterns (too many, too long, an offset past 32 bits, or
+// two sequences with one hash).  Which slot a pattern gets can differ from run
+// to run; what it holds cannot.
+constexpr int kPatExact = 7;
+
+__device__ __forceinline__ unsigned long long pat_mix(unsigned long long h) {
+    h *= 0x9E3779B97F4A7C15ull;
+    return h ^ (h >> 29);
+}
+
+// Key of the row with codes [a, a + len); never 0.
+__device__ __forceinline__ unsigned long long pat_key(const uint8_t *codes, int64_t a, int len) {
+    unsigned long long w = 0;
+    if (len <= kPatExact) {
+#pragma unroll
+        for (int j = 0; j < kPatExact; ++j) {
+            const unsigned long long c = codes[a + (j < len ? j : 0)];   // every lane loads (len 0: some code)
+            w |= j < len ? c << (8 * j) : 0ull;
+        }
+        return w | static_cast<unsigned long long>(len + 1) << 56;
+    }
+    unsigned long long h = pat_mix(0x2545F4914F6CDD1Dull + len);
+    for (int j = 0; j < len; ++j) h = pat_mix(h ^ (codes[a + j] + 1ull));
+    return h | 0xff00000000000000ull;   // apart from the exact keys
+}
+
+__global__ __launch_bounds__(kBlock) void k_pat_clear(unsigned long long *keys, unsigned *words) {
+    keys[threadIdx.x] = 0;
+    if (threadIdx.x < 4) words[threadIdx.x] = 0;
+}
+
+// Lane `lane`'s value (readlane returns a signed word: each half is made
+// unsigned before the two are joined).
+__device__ __forceinline__ unsigned long long lane_word(unsigned long long v, int lane) {
+    const unsigned lo = __builtin_amdgcn_readlane(static_cast<unsigned>(v), lane);
+    const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(v >> 32), lane);
+    return static_cast<unsigned long long>(hi) << 32 | lo;
+}
+
+// The slot of this wave's rows' keys (every lane of the wave calls this; live:
+// the lane has a row), one distinct key at a time, so one lane at most goes to
+// the global table for it (all of them, and the device's first row tiles at
+// once, serialise on one address: 5.8 ms at stencil7 N = 215).
+__device__ __forceinline__ int pat_slot(unsigned long long key, int64_t row, bool live, unsigned long long *seen,
+                                        unsigned long long *keys, int64_t *rows) {
+    int slot = -1;
+    unsigned long long left = __ballot(live);
+    while (left != 0) {
+        const int leader = __builtin_ctzll(left);
+        const unsigned long long k0 = lane_word(key, leader);
+        unsigned h = static_cast<unsigned>(pat_mix(k0) >> 56);
+        int found = -1;
+        for (int probe = 0; probe < kPatterns && found < 0; ++probe, h = (h + 1u) & (kPatterns - 1u)) {
+            unsigned long long k = seen[h];
+            if (k == 0) {
+                k = __hip_atomic_load(keys + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (k == 0) {
+                    unsigned long long old = 0;
+                    if ((threadIdx.x & 63) == static_cast<unsigned>(leader)) {
+                        old = atomicCAS(keys + h, 0ull, k0);
+                        if (old == 0) rows[h] = row;
+                    }
+                    old = lane_word(old, leader);
+                    k = old == 0 ? k0 : old;
+                }
+                seen[h] = k;    // whoever gets here stores the same key
+            }
+            if (k == k0) found = static_cast<int>(h);
+        }
+        const bool mine = live && key == k0;
+        if (mine) slot = found;
+        left &= ~(__ballot(mine) | 1ull << leader);   // the leader's key is its own: the loop ends
+    }
+    return slot;
+}
+
+// Workgroup w takes the 256 rows from w * lead on and those `step` rows further,
+// again and again; with pat null the keys only (a few workgroups ahead of the
+// rest, so that the usual keys are there when every workgroup starts).
+__global__ __launch_bounds__(kBlock) void k_pat_scan(int64_t n, const RowPack *__restrict__ rp,
+                                                     const uint8_t *__restrict__ codes, unsigned long long *keys,
+                                                     int64_t *rows, int64_t lead, int64_t step,
+                                                     uint8_t *__restrict__ pat,
+                                                     unsigned *words) {
+    static_assert(kPatterns == kBlock, "a thread per slot");
+    __shared__ unsigned long long seen[kPatterns];
+    seen[threadIdx.x] = 0;
+    __syncthreads();
+    bool bad = false;
+    for (int64_t r0 = blockIdx.x * lead; r0 < n; r0 += step) {
+        const int64_t row = r0 + threadIdx.x;
+        const bool has = row < n;
+        int64_t a = 0, b = 0;
+        if (has) row_range(rp, n, row, a, b);
+        const bool fits = has && b - a <= kPatternRow;
+        const unsigned long long key = fits ? pat_key(codes, a < b ? a : 0, static_cast<int>(b - a)) : 0ull;
+        const int slot = pat_slot(key, row, fits, seen, keys, rows);
+        bad = bad || (has && slot < 0);
+        if (pat && has && slot >= 0) pat[row] = static_cast<uint8_t>(slot);
+        if (__any(bad)) break;   // no patterns
+    }
+    if (bad) atomicOr(&words[1], 1u);
+}
+
+__global__ __launch_bounds__(kBlock) void k_pat_table(int64_t n, const RowPack *__restrict__ rp,
+                                                      const uint8_t *__restrict__ codes,
+                                                      const int64_t *__restrict__ dict,
+                                                      const unsigned long long *__restrict__ keys,
+                                                      const int64_t *__restrict__ rows, RowPatterns *out,
+                                                      unsigned *words) {
+    __shared__ int start[kPatterns];
+    if (words[1] != 0) return;   // uniform
+    const int i = threadIdx.x;
+    int64_t a = 0, b = 0;
+    if (keys[i] != 0) row_range(rp, n, rows[i], a, b);
+    const int len = static_cast<int>(b - a);
+    start[i] = len;
+    __syncthreads();
+    int at = 0, all = 0;
+    for (int j = 0; j < kPatterns; ++j) {
+        at += j < i ? start[j] : 0;
+        all += start[j];
+    }
+    if (all > kPatternOffs) {   // uniform
+        if (i == 0) words[1] = 1;
+        return;
+    }
+    out->info[i] = static_cast<uint32_t>(at) | static_cast<uint32_t>(len) << 16;
+    for (int j = 0; j < len; ++j) {
+        const int64_t d = dict[codes[a + j]];
+        if (d > INT32_MAX || d < INT32_MIN) atomicOr(&words[1], 1u);
+        out->offs[at + j] = static_cast<int32_t>(d);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_pat_verify(int64_t n, const RowPack *__restrict__ rp,
+                                                       const uint8_t *__restrict__ codes,
+                                                       const int64_t *__restrict__ dict,
+                                                       const RowPatterns *__restrict__ tab,
+                                                       const uint8_t *__restrict__ pat, unsigned *words) {
+    __shared__ int64_t off[kCodeDict];
+    __shared__ uint32_t info[kPatterns];
+    __shared__ int32_t offs[kPatternOffs];
+    if (words[1] != 0) return;   // uniform
+    for (int i = threadIdx.x; i < kCodeDict; i += kBlock) off[i] = dict[i];
+    for (int i = threadIdx.x; i < kPatterns; i += kBlock) info[i] = tab->info[i];
+    for (int i = threadIdx.x; i < kPatternOffs; i += kBlock) offs[i] = tab->offs[i];
+    __syncthreads();
+    bool same = true;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+    for (int64_t row = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; row < n; row += stride) {
+        int64_t a, b;
+        row_range(rp, n, row, a, b);
+        const uint32_t w = info[pat[row]];
+        const int len = static_cast<int>(w >> 16);
+        const int32_t *o = offs + (w & 0xffffu);
+        same = same && b - a == len;
+        for (int j = 0; j < len && same; ++j) same = off[codes[a + j]] == o[j];
+    }
+    if (!same) atomicOr(&words[1], 2u);
+}
+
 // COO structure: row and column indices in range, rows non-decreasing.
 template <typename I>
 __global__ __launch_bounds__(kBlock) void k_coo_validate(int64_t n_rows, int64_t n_cols, int64_t nnz,
@@ -1004,6 +1176,36 @@ hipError_t launch_code_build(const CsrDev &A, int step, long long *table, unsign
                            reinterpret_cast<uint16_t *>(tb + (A.n_rows + kTileRows - 1) / kTileRows + 1), words);
         return hipGetLastError();
     });
+}
+
+size_t pattern_buffer_bytes(int64_t n_rows) {
+    return (sizeof(unsigned long long) + sizeof(int64_t)) * kPatterns + sizeof(RowPatterns) +
+           ((static_cast<size_t>(n_rows) + 15) & ~size_t(15));
+}
+
+const void *pattern_bytes(void *buf) {
+    return static_cast<char *>(buf) + (sizeof(unsigned long long) + sizeof(int64_t)) * kPatterns + sizeof(RowPatterns);
+}
+
+hipError_t launch_pattern_build(const CsrDev &A, unsigned *words, void *buf, int grid, hipStream_t s) {
+    if (!A.codes || !A.rowpack || A.n_rows < 1 || A.nnz < 1) return hipErrorInvalidValue;
+    const RowPack *rp = static_cast<const RowPack *>(A.rowpack);
+    const uint8_t *codes = static_cast<const uint8_t *>(A.codes);
+    const int64_t *dict = reinterpret_cast<const int64_t *>(codes) - kCodeDict;
+    unsigned long long *keys = static_cast<unsigned long long *>(buf);
+    int64_t *rows = reinterpret_cast<int64_t *>(keys + kPatterns);
+    RowPatterns *tab = reinterpret_cast<RowPatterns *>(rows + kPatterns);
+    uint8_t *pat = reinterpret_cast<uint8_t *>(tab + 1);
+    hipLaunchKernelGGL(k_pat_clear, dim3(1), dim3(kBlock), 0, s, keys, words);
+    const int64_t sixteenth = ((A.n_rows + 15) / 16 + kBlock - 1) / kBlock * kBlock;
+    hipLaunchKernelGGL(k_pat_scan, dim3(16), dim3(kBlock), 0, s, A.n_rows, rp, codes, keys, rows, sixteenth,
+                       16 * sixteenth, static_cast<uint8_t *>(nullptr), words);
+    hipLaunchKernelGGL(k_pat_scan, dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, codes, keys, rows,
+                       static_cast<int64_t>(kBlock), static_cast<int64_t>(grid) * kBlock, pat, words);
+    hipLaunchKernelGGL(k_pat_table, dim3(1), dim3(kBlock), 0, s, A.n_rows, rp, codes, dict, keys, rows, tab, words);
+    if (A.max_row > kPatExact || A.max_row == 0)
+        hipLaunchKernelGGL(k_pat_verify, dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, codes, dict, tab, pat, words);
+    return hipGetLastError();
 }
 
 hipError_t launch_rowpack(const CsrDev &A, void *rows, unsigned *words, int grid, hipStream_t s) {
@@ -1278,6 +1480,14 @@ int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t) {
         } else {
             q(k_spmv_split<float, float, float, EpiPq<float>>);
             q(k_spmv_split<float, float, float, EpiPlain<float>>);
+        }
+    } else if (t.kind == 0 && t.pats && A.patterns) {
+        if (A.val_t == 0) {
+            q(k_spmv_pattern<double, double, double, EpiPq<double>>);
+            q(k_spmv_pattern<double, double, double, EpiPlain<double>>);
+        } else {
+            q(k_spmv_pattern<float, float, float, EpiPq<float>>);
+            q(k_spmv_pattern<float, float, float, EpiPlain<float>>);
         }
     } else if (t.kind == 0 && t.codes && A.codes) {   // the coded instances the launch will use
         const bool pack = t.pack && A.rowpack;

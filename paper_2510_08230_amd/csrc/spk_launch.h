@@ -36,6 +36,12 @@ hipError_t launch_pattern_probe(const CsrDev &A, int step, long long *table, uns
 // codes_base holds code_buffer_bytes(n_rows, nnz) bytes.
 hipError_t launch_code_build(const CsrDev &A, int step, long long *table, unsigned *words, void *codes_base,
                              int grid, hipStream_t s);
+// Row patterns of a matrix with codes and packed row pointers (plan time):
+// buf holds pattern_buffer_bytes; pattern_bytes(buf) becomes
+// CsrDev::patterns unless words[1] is nonzero afterwards.
+size_t pattern_buffer_bytes(int64_t n_rows);
+const void *pattern_bytes(void *buf);
+hipError_t launch_pattern_build(const CsrDev &A, unsigned *words, void *buf, int grid, hipStream_t s);
 // Packed row pointers (rowpack_bytes(n_rows)) on their own: words[1] must be 0;
 // words[2] is set when a row offset within its tile exceeds 65535.
 hipError_t launch_rowpack(const CsrDev &A, void *rows, unsigned *words, int grid, hipStream_t s);

@@ -356,6 +356,137 @@ __global__ __launch_bounds__(kBlock) void k_spmv_vector(int64_t n, const P *__re
     epi.finish();
 }
 
+// ---- row patterns (RowPatterns) ---------------------------------------------------
+// A structured grid's rows repeat a few sequences of column offsets (a 7-point
+// stencil's 27), so one byte per row names them all, and in a wave whose rows
+// share one sequence the offsets are scalars: an entry costs one LDS read (its
+// value) and one load at a scalar base, where a column code costs three LDS
+// reads and 64-bit address arithmetic per lane.  That row work, not the
+// stream, is what the coded tiles wait for (stencil7 N = 215 FP64: tiles
+// streamed into LDS alone 97 us, with the row sums 150).  Rows sum in storage
+// order: products equal the coded ones bit for bit.
+struct PatMeta {
+    TileMeta<RowPack> rows;
+    uint8_t id;
+    __device__ __forceinline__ void load(const RowPack *__restrict__ rp, const uint8_t *__restrict__ pat, int64_t n,
+                                         int64_t tile) {
+        rows.load(rp, n, tile);
+        const int64_t row = tile * kTileRows + threadIdx.x;
+        id = pat[row < n ? row : n - 1];
+    }
+};
+
+// Waves per SIMD the kernel is held to (without spills): FP64 vectors seven
+// (the LDS of a CU holds seven workgroups too), FP32 eight; the loop's product
+// lands at four to six when left to the compiler.
+template <typename C>
+constexpr int pattern_min_waves() {
+    return std::is_same_v<C, double> ? 7 : 8;
+}
+
+template <typename V, typename X, typename C, class Epi>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(pattern_min_waves<C>()))) void
+k_spmv_pattern(int64_t n, int64_t nnz, const RowPack *__restrict__ rp, const uint8_t *__restrict__ pat,
+               const V *__restrict__ va, const X *__restrict__ x, int remap, int nt, int walkers, Epi epi_in) {
+    Epi epi = epi_in;
+    if (epi.skip()) return;
+    const uint32_t W = walkers > 0 && static_cast<uint32_t>(walkers) < gridDim.x ? walkers : gridDim.x;
+    if (blockIdx.x >= W) {   // uniform
+        epi.finish();
+        return;
+    }
+    __shared__ u32x4 lv[Chunks<V>::LDS];
+    __shared__ uint32_t info[kPatterns];
+    __shared__ int32_t offs[kPatternOffs];
+    const RowPatterns *tab = reinterpret_cast<const RowPatterns *>(pat) - 1;
+    for (int i = threadIdx.x; i < kPatterns; i += kBlock) info[i] = tab->info[i];
+    for (int i = threadIdx.x; i < kPatternOffs; i += kBlock) offs[i] = tab->offs[i];
+    __syncthreads();
+    const V *sv = reinterpret_cast<const V *>(lv);
+    const int64_t T = (n + kTileRows - 1) / kTileRows;
+    TileIter it(T, remap, W);
+    if (it.valid()) {
+        PatMeta cur, nxt;
+        cur.load(rp, pat, n, it.tile());
+        while (true) {
+            TileIter after = it;
+            after.next();
+            const bool more = after.valid();
+            const int64_t r0 = cur.rows.r0;
+            const int64_t r1 = min(r0 + static_cast<int64_t>(kTileRows), n);
+            const int64_t row = r0 + threadIdx.x;
+            const int64_t s = cur.rows.first(), e = cur.rows.end();
+            const bool staged = e - s <= kStreamCap;   // uniform
+            if (staged) dma_chunks<V>(va, s, e, nnz, lv, nt);
+            if (more) nxt.load(rp, pat, n, after.tile());
+            const auto pv = pre_of(epi, row < r1 ? row : r1 - 1);
+            if (staged) {
+                __builtin_amdgcn_s_waitcnt(0);
+                __syncthreads();
+                __builtin_amdgcn_s_setprio(2);   // (as in spmv_tiles_lds)
+                if (row < r1) {
+                    // this row's values, from its first one on
+                    const V *v = sv + (cur.rows.lo() - (s & ~static_cast<int64_t>(Chunks<V>::EPC - 1)));
+                    const int id = __builtin_amdgcn_readfirstlane(cur.id);
+                    C sum = 0;
+                    constexpr int U = 8;
+                    if (__all(cur.id == id)) {
+                        const uint32_t w = __builtin_amdgcn_readfirstlane(tab->info[id]);
+                        const int32_t *o = tab->offs + (w & 0xffffu);
+                        const int len = static_cast<int>(w >> 16);
+                        const X *xr = x + r0;
+                        for (int j0 = 0; j0 < len; j0 += U) {
+                            C xv[U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                xv[u] = 0;
+                                if (j0 + u < len) xv[u] = static_cast<C>((xr + o[j0 + u])[threadIdx.x]);
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u)
+                                if (j0 + u < len) sum = fma(static_cast<C>(widen(v[j0 + u])), xv[u], sum);
+                        }
+                    } else {
+                        const uint32_t w = info[cur.id];
+                        const int32_t *o = offs + (w & 0xffffu);
+                        const int len = static_cast<int>(w >> 16);
+                        for (int j0 = 0; j0 < len; j0 += kRowUnroll) {
+                            C av[kRowUnroll], xv[kRowUnroll];
+#pragma unroll
+                            for (int u = 0; u < kRowUnroll; ++u) {
+                                av[u] = 0;
+                                xv[u] = 0;
+                                if (j0 + u < len) {
+                                    av[u] = static_cast<C>(widen(v[j0 + u]));
+                                    xv[u] = static_cast<C>(x[row + o[j0 + u]]);
+                                }
+                            }
+#pragma unroll
+                            for (int u = 0; u < kRowUnroll; ++u) sum = fma(av[u], xv[u], sum);
+                        }
+                    }
+                    emit_row(epi, row, sum, pv);
+                }
+                __builtin_amdgcn_s_setprio(0);
+                lds_barrier();
+            } else if (row < r1) {
+                const uint32_t w = info[cur.id];
+                const int32_t *o = offs + (w & 0xffffu);
+                const int len = static_cast<int>(w >> 16);
+                const V *v = va + cur.rows.lo();
+                C sum = 0;
+                for (int j = 0; j < len; ++j)
+                    sum = fma(static_cast<C>(widen(ldv(v + j, nt))), static_cast<C>(x[row + o[j]]), sum);
+                emit_row(epi, row, sum, pv);
+            }
+            if (!more) break;
+            it = after;
+            cur = nxt;
+        }
+    }
+    epi.finish();
+}
+
 // ---- split gathers (SplitDev) ----------------------------------------------------
 // A random pattern's product is bound by the lines its gathers fill: at 1e7
 // columns nearly every 8-byte read brings a 128-byte line through the fabric
@@ -602,6 +733,17 @@ hipError_t launch_family(const CsrDev &A, const SpmvTune &t, const X *x, const E
             hipLaunchKernelGGL(K, dim3(t.grid), dim3(kBlock), 0, s, A.n_rows, A.nnz, A.ci, A.idx_t, static_cast<const V *>(A.va),
                                x, A.split, t.xcd_remap, t.nt, walk, epi,
                                LongArg<2>{A.pieces ? A.long_base : nullptr, A.piece_sums});
+            return hipGetLastError();
+        }
+    }
+    if constexpr (!HasGather<Epi>::value) {
+        if (t.kind == 0 && t.pats && A.patterns && (reinterpret_cast<uintptr_t>(A.va) & 15) == 0) {
+            constexpr auto K = k_spmv_pattern<V, X, C, Epi>;
+            const int per_cu = resident_per_cu<K>();
+            const int walk = t.cus > 0 && per_cu > 0 ? std::min(t.grid, t.cus * per_cu) : 0;
+            hipLaunchKernelGGL(K, dim3(t.grid), dim3(kBlock), 0, s, A.n_rows, A.nnz,
+                               static_cast<const RowPack *>(A.rowpack), static_cast<const uint8_t *>(A.patterns),
+                               static_cast<const V *>(A.va), x, t.xcd_remap, t.nt, walk, epi);
             return hipGetLastError();
         }
     }
