@@ -276,32 +276,59 @@ __global__ __launch_bounds__(kBlock) void k_gm_passA(int64_t n, int64_t ld, cons
     block_partial<NV>(acc, part);
 }
 
-// Partial sums of one coefficient per workgroup: out[t] = sum of part row t.
-__global__ __launch_bounds__(kBlock) void k_gm_reduce(const double *part, int G, double *out, const SolveState *st,
-                                                      const GmresState *gs) {
-    if (gm_idle(st, gs)) return;
-    const int t = blockIdx.x;
-    double tot[1];
-    sum_partials<1>(part + static_cast<int64_t>(t) * kMaxGrid, G, tot);
-    if (threadIdx.x == 0) out[t] = tot[0];
+// The scalar work between the passes, one workgroup of kMidThreads: a wave
+// sums a row of partials at a time, and the small dense work (J <= 33 terms)
+// runs a term per lane.  One launch each where there were two, a reduction
+// with a workgroup per row and a one-thread kernel (stencil7_ns N = 215,
+// mean per step: 4.5 + 14 and 4.5 + 10 us, most of it that thread's chain of
+// loads; 5 and 6 us now).
+constexpr int kMidThreads = 1024;
+
+// out[t] = sum of part row t (t < rows), in every thread's LDS view after the
+// call: each lane its strided share in order, then the wave.
+__device__ __forceinline__ void sum_rows(const double *part, int G, int rows, double *out) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    constexpr int U = 8;
+    for (int t = wid; t < rows; t += kMidThreads / 64) {
+        const double *p = part + static_cast<int64_t>(t) * kMaxGrid;
+        double v = 0.0;
+        for (int b0 = lane; b0 < G; b0 += 64 * U) {
+            double x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = p[b0 + 64 * u < G ? b0 + 64 * u : b0];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (b0 + 64 * u < G) v += x[u];
+        }
+        v = wave_sum(v);
+        if (lane == 0) out[t] = v;
+    }
+    __syncthreads();
 }
 
-// Step coefficients (one thread; J <= 33 terms): h (column j before the
-// delayed correction) and d (u_{j+1} = w / nu - sum d_t q_t, t <= j).
-__global__ void k_gm_coef(const SolveState *st, GmresState *gs, int j) {
-    if (gm_idle(st, gs) || threadIdx.x != 0 || blockIdx.x != 0) return;
+// b (first pass), then the step's coefficients: h (column j before the delayed
+// correction) and d (u_{j+1} = w / nu - sum d_t q_t, t <= j).
+__global__ __launch_bounds__(kMidThreads) void k_gm_coef(const SolveState *st, GmresState *gs, const double *part, int G,
+                                                         int j) {
+    if (gm_idle(st, gs)) return;
+    __shared__ double b[kMaxKrylov + 1];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const double inv = 1.0 / gs->nu;
-    double qwj = gs->b[j];   // u_j . w  ->  q_j . w
-    for (int t = 0; t < j; ++t) qwj = fma(-gs->a[t], gs->b[t], qwj);
-    qwj *= inv;
-    for (int s = 0; s <= j; ++s) {
+    const double at = lane < j ? gs->a[lane] : 0.0;   // j <= 32
+    sum_rows(part, G, j + 1, b);
+    for (int s = wid; s <= j; s += kMidThreads / 64) {
         // e_s = sum_{t < j} Hu[s][t] a_t (Hu[s][t] = 0 for s > t + 1)
-        double e = 0.0;
-        for (int t = s > 0 ? s - 1 : 0; t < j; ++t) e = fma(gs->Hu[s * kMaxKrylov + t], gs->a[t], e);
-        const double qw = s < j ? gs->b[s] : qwj;
+        const bool in = lane < j && lane + 1 >= s;
+        const double e = wave_sum(in ? gs->Hu[s * kMaxKrylov + lane] * at : 0.0);
+        double qw = b[s];
+        if (s == j)   // u_j . w  ->  q_j . w
+            qw = (qw - wave_sum(lane < j ? at * b[lane] : 0.0)) * inv;
         const double h = (qw - e) * inv;
-        gs->h[s] = h;
-        gs->d[s] = fma(e, inv, h);
+        if (lane == 0) {
+            gs->b[s] = b[s];
+            gs->h[s] = h;
+            gs->d[s] = fma(e, inv, h);
+        }
     }
 }
 
@@ -501,32 +528,39 @@ __global__ __launch_bounds__(kBlock) void k_gm_passB(int64_t n, int64_t ld, cons
     }
 }
 
-// End of step j (one workgroup; thread 0 does the scalar work): nu' from
-// ||u_{j+1}||^2 (partials row nvrow) and a'; column j of Hu and of the
-// rotated H; earlier rotations, a new rotation, g, the residual estimate and
-// the stop test.
-__global__ __launch_bounds__(kBlock) void k_gm_final(SolveState *st, GmresState *gs, const double *part, int G,
-                                                     int nvrow, int j, int m) {
+// End of step j: a' (second pass), nu' from ||u_{j+1}||^2 (partials row nvrow)
+// and a'; column j of Hu and of the rotated H; earlier rotations, a new
+// rotation, g, the residual estimate and the stop test.
+__global__ __launch_bounds__(kMidThreads) void k_gm_final(SolveState *st, GmresState *gs, const double *part, int G,
+                                                          int nvrow, int j, int m) {
     if (gm_idle(st, gs)) return;
-    double tot[1];
-    sum_partials<1>(part + static_cast<int64_t>(nvrow) * kMaxGrid, G, tot);
-    if (threadIdx.x != 0) return;
-    double s2 = 0.0;
-    for (int t = 0; t <= j; ++t) s2 = fma(gs->a[t], gs->a[t], s2);
-    const double hn = sqrt(fmax(tot[0] - s2, 0.0));
-    double *H = gs->H;
-    for (int t = 0; t <= j; ++t) {
-        const double c = gs->h[t] + gs->a[t];
-        gs->Hu[t * kMaxKrylov + j] = c;
-        H[t * kMaxKrylov + j] = c;
+    __shared__ double a1[kMaxKrylov + 1], col[kMaxKrylov + 1], cs[kMaxKrylov], sn[kMaxKrylov], un[1];
+    const int tid = threadIdx.x;
+    if (tid < j) {
+        cs[tid] = gs->cs[tid];
+        sn[tid] = gs->sn[tid];
     }
+    const double ht = tid <= j ? gs->h[tid] : 0.0;
+    sum_rows(part + static_cast<int64_t>(nvrow) * kMaxGrid, G, 1, un);
+    sum_rows(part, G, j + 1, a1);
+    if (tid >= 64) return;   // one wave does the rest
+    const double at = tid <= j ? a1[tid] : 0.0;
+    const double hn = sqrt(fmax(un[0] - wave_sum(at * at), 0.0));
+    if (tid <= j) {
+        const double c = ht + at;
+        gs->a[tid] = at;
+        gs->Hu[tid * kMaxKrylov + j] = c;
+        col[tid] = c;
+    }
+    if (tid != 0) return;
     gs->Hu[(j + 1) * kMaxKrylov + j] = hn;
+    double *H = gs->H;
+    double a = col[0];
     for (int t = 0; t < j; ++t) {
-        const double a = H[t * kMaxKrylov + j], c = H[(t + 1) * kMaxKrylov + j];
-        H[t * kMaxKrylov + j] = gs->cs[t] * a + gs->sn[t] * c;
-        H[(t + 1) * kMaxKrylov + j] = -gs->sn[t] * a + gs->cs[t] * c;
+        const double c = col[t + 1];
+        H[t * kMaxKrylov + j] = cs[t] * a + sn[t] * c;
+        a = -sn[t] * a + cs[t] * c;
     }
-    const double a = H[j * kMaxKrylov + j];
     const double d = hypot(a, hn);
     double c = 1.0, s = 0.0;
     if (d != 0.0) {
@@ -537,10 +571,11 @@ __global__ __launch_bounds__(kBlock) void k_gm_final(SolveState *st, GmresState 
     gs->sn[j] = s;
     H[j * kMaxKrylov + j] = c * a + s * hn;
     H[(j + 1) * kMaxKrylov + j] = 0.0;
-    gs->g[j + 1] = -s * gs->g[j];
-    gs->g[j] = c * gs->g[j];
+    const double gj = gs->g[j];
+    gs->g[j + 1] = -s * gj;
+    gs->g[j] = c * gj;
     const int64_t k = st->iter + 1;
-    const double res = fabs(gs->g[j + 1]);
+    const double res = fabs(s * gj);
     st->iter = k;
     st->resnorm = res;
     if (st->hist && k < st->hist_cap) st->hist[k] = res;
@@ -554,15 +589,24 @@ __global__ __launch_bounds__(kBlock) void k_gm_final(SolveState *st, GmresState 
     if (stop != STOP_RUNNING) st->stop = stop;
 }
 
-// R y = g by back substitution over the columns built (one thread).
-__global__ void k_gm_solve(const SolveState *st, GmresState *gs) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int used = gs->used;
+// R y = g by back substitution over the columns built, a row per lane: once
+// y_i is known every row above takes its term off (one thread with the terms
+// row by row: 42 us at 30 columns).
+__global__ __launch_bounds__(64) void k_gm_solve(const SolveState *st, GmresState *gs) {
+    const int used = gs->used, lane = threadIdx.x;
     if (st->stop == STOP_NON_FINITE || used == 0) return;
+    __shared__ double R[kMaxKrylov * (kMaxKrylov + 1)];   // column i from i * (kMaxKrylov + 1) on
+    for (int k = lane; k < used * used; k += 64) {
+        const int i = k / used, t = k % used;
+        R[t * (kMaxKrylov + 1) + i] = gs->H[i * kMaxKrylov + t];
+    }
+    double g = lane < used ? gs->g[lane] : 0.0;
+    __syncthreads();
     for (int i = used - 1; i >= 0; --i) {
-        double s = gs->g[i];
-        for (int t = i + 1; t < used; ++t) s -= gs->H[i * kMaxKrylov + t] * gs->y[t];
-        gs->y[i] = s / gs->H[i * kMaxKrylov + i];
+        const double *ri = R + i * (kMaxKrylov + 1);
+        const double y = __shfl(g, i, 64) / ri[i];
+        if (lane < i) g -= ri[lane] * y;
+        if (lane == i) gs->y[i] = y;
     }
 }
 
@@ -718,8 +762,7 @@ static hipError_t step_rest_t(int64_t n, int grid, T *V, T *w, int j, int m, Sol
     if (nv == 8) launch_passA<T, 8>(grid, n, ld, V, w, j, st, gs, gpart, s);
     else if (nv == 16) launch_passA<T, 16>(grid, n, ld, V, w, j, st, gs, gpart, s);
     else launch_passA<T, 32>(grid, n, ld, V, w, j, st, gs, gpart, s);
-    hipLaunchKernelGGL(k_gm_reduce, dim3(J), dim3(kBlock), 0, s, gpart, grid, &gs->b[0], st, gs);
-    hipLaunchKernelGGL(k_gm_coef, dim3(1), dim3(64), 0, s, st, gs, j);
+    hipLaunchKernelGGL(k_gm_coef, dim3(1), dim3(kMidThreads), 0, s, st, gs, gpart, grid, j);
     // passB: lanes per pack by basis bucket
     if (nv == 8)
         hipLaunchKernelGGL((k_gm_passB<T, 8, passb_split<T, 8>()>), dim3(grid), dim3(kBlock), 0, s, n, ld, V, uj, un,
@@ -730,8 +773,7 @@ static hipError_t step_rest_t(int64_t n, int grid, T *V, T *w, int j, int m, Sol
     else
         hipLaunchKernelGGL((k_gm_passB<T, 32, passb_split<T, 32>()>), dim3(grid), dim3(kBlock), 0, s, n, ld, V, uj,
                            un, w, j, st, gs, gpart);
-    hipLaunchKernelGGL(k_gm_reduce, dim3(J), dim3(kBlock), 0, s, gpart, grid, &gs->a[0], st, gs);
-    hipLaunchKernelGGL(k_gm_final, dim3(1), dim3(kBlock), 0, s, st, gs, gpart, grid, nv, j, m);
+    hipLaunchKernelGGL(k_gm_final, dim3(1), dim3(kMidThreads), 0, s, st, gs, gpart, grid, nv, j, m);
     return hipGetLastError();
 }
 
