@@ -259,28 +259,28 @@ SpmvTune heuristic_tune(spk_ctx ctx, const CsrDev &A) {
 }
 
 // The column blocks (2^result columns) of a split of A's gathers, or -1 for
-// none.  vt: the value type of its products (FP32 vectors for all but F64).
+// none.  f64: some of its products have FP64 vectors.
 // An irregular pattern (no column codes) with tiles that mostly fit LDS (at
 // most 7.5 entries per row on average) and 32-bit stream positions.  Blocks of
 // 128 KB of the vector are gathered from LDS; when those would be more than
-// kSplitBlocks, blocks of 2^16 to 2^19 columns from L2.  Below 2^22 entries
+// kSplitBlocks, blocks of 2^17 to 2^19 columns from L2.  Below 2^22 entries
 // plans keep the plain product, whose launch the allocation-free solve shares
 // (and the vector fits an XCD's 4 MB L2).  SPK_SPLIT=0 turns it off, 1 lifts
 // the size limits (tests).
-int split_shift(const CsrDev &A, int vt) {
+int split_shift(const CsrDev &A, bool f64) {
     const char *env = std::getenv("SPK_SPLIT");
     if (env && std::strcmp(env, "0") == 0) return -1;
     const bool forced = env && std::strcmp(env, "1") == 0;
     if (A.codes || !stream_ok(A) || A.n_rows < 1 || A.n_cols < 1 || A.nnz < 1 || A.nnz > INT32_MAX) return -1;
     if (!forced && (A.nnz > 7.5 * A.n_rows || A.nnz < (int64_t(1) << 22))) return -1;
-    for (int shift : {vt == SPK_F64 ? 14 : 15, 16, 17, 18, 19})
+    for (int shift : {f64 ? spk::kSplitLocal - 1 : spk::kSplitLocal, 17, 18, 19})
         if (((A.n_cols - 1) >> shift) < spk::kSplitBlocks) return shift;
     return -1;
 }
 
 TuneKey tune_key(const CsrDev &A, int use) {
     return TuneKey{A.n_rows, A.n_cols, A.nnz, A.ptr_t, A.idx_t, A.val_t, use, A.codes != nullptr, stream_ok(A),
-                   A.max_row > spk::kLongRow, A.split.xg != nullptr || split_shift(A, A.val_t) >= 0};
+                   A.max_row > spk::kLongRow, A.split.xg != nullptr || split_shift(A, true) >= 0};
 }
 
 // Times each candidate and keeps the fastest.  x, y: device vectors of the
@@ -564,11 +564,14 @@ spk_status build_patterns(spk_plan pl) {
 }
 
 // The split of A's gathers, where split_shift allows one and the tuner has not
-// already timed this shape and found it slower.  Without memory for it the products gather as they go.
+// already timed this shape and found it slower.  vt: the value type of the
+// products that are tuned.  Without memory for it the products gather as they
+// go.
 spk_status build_split(spk_plan pl, int use, int vt) {
     spk_ctx ctx = pl->ctx;
     CsrDev &A = pl->A;
-    const int shift = split_shift(A, vt);
+    // a solve computes its true residuals in FP64, whatever its values are
+    const int shift = split_shift(A, use != TUNE_PLAIN || vt == SPK_F64);
     if (shift < 0) return SPK_OK;
     const char *forced = std::getenv("SPK_SPMV_KERNEL");
     if (forced && *forced && !std::strstr(forced, "split=1")) return SPK_OK;
@@ -578,7 +581,7 @@ spk_status build_split(spk_plan pl, int use, int vt) {
     if (hit != ctx->tune_cache.end() && !hit->second.tune.split) return SPK_OK;
     const int blocks = static_cast<int>((A.n_cols - 1) >> shift) + 1;
     void *buf = nullptr;
-    if (ctx->dpool.get(spk::split_buffer_bytes(A.n_rows, A.nnz, blocks), &buf) != hipSuccess) return SPK_OK;
+    if (ctx->dpool.get(spk::split_buffer_bytes(A.n_rows, A.nnz, blocks, shift), &buf) != hipSuccess) return SPK_OK;
     spk::SplitDev d;
     const uint32_t *count = nullptr;
     unsigned *words = reinterpret_cast<unsigned *>(ctx->d_probe + spk::kCodeSlots);

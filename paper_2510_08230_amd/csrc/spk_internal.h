@@ -158,22 +158,27 @@ struct SpmvTune {
 
 // The gathers of an irregular product, taken in an order of their own.  The
 // entries of the row tiles (those of at most kStreamCap entries) are listed by
-// column block (2^shift columns), within a block by tile: the stream.  A first
-// launch reads x[cols[j]] for every stream position j into xg[j], a block's
-// slice of x at a time; the row tiles then read their segments of xg (one per
-// block) and pick entry k's value at place perm[k] of them.
+// column block (2^shift columns), within a block by group of kSplitGroup
+// tiles: the stream.  A first launch reads x[cols[j]] for every stream
+// position j into xg[j], a block's slice of x at a time.  A row tile then
+// reads its values of xg into LDS, place p of the tile that starts at entry s
+// from xg[src[s + p]] (in block order, so neighbouring places read
+// neighbouring words), and takes entry k's from place perm[k].
 struct SplitDev {
     void *xg = nullptr;              // one value of x per stream position (8 bytes each)
-    const int32_t *cols = nullptr;   // stream position -> column
-    const uint16_t *perm = nullptr;  // entry -> place in its tile's segments
-    const uint32_t *seg = nullptr;   // [tile][block]: the segment's first stream position
-    const uint16_t *off = nullptr;   // [tile][block], blocks + 1 each: its first place
+    const void *cols = nullptr;      // stream position -> column: uint16 within its block up to
+                                     // kSplitLocal, else int32
+    const uint32_t *src = nullptr;   // tile place -> stream position
+    const uint16_t *perm = nullptr;  // entry -> tile place
+    const uint32_t *start = nullptr; // block -> its first stream position (blocks + 1)
     const void *rows = nullptr;      // packed row pointers (as CsrDev::rowpack)
     int64_t count = 0;               // stream positions
     int blocks = 0, shift = 0;
 };
 
-constexpr int kSplitBlocks = 128;    // most column blocks (two per lane of a wave)
+constexpr int kSplitBlocks = 1024;   // most column blocks
+constexpr int kSplitLocal = 15;      // largest shift of the blocks gathered from LDS
+constexpr int kSplitGroup = 4;       // row tiles whose entries of a block are listed together
 
 // Device CSR view with runtime-typed arrays.
 struct CsrDev {

@@ -49,7 +49,7 @@ hipError_t launch_rowpack(const CsrDev &A, void *rows, unsigned *words, int grid
 // n_cols; buf holds split_buffer_bytes.  *out describes the structure except
 // its count, which *count points to on the device; words as for
 // launch_rowpack.
-size_t split_buffer_bytes(int64_t n_rows, int64_t nnz, int blocks);
+size_t split_buffer_bytes(int64_t n_rows, int64_t nnz, int blocks, int shift);
 hipError_t launch_split_build(const CsrDev &A, int blocks, int shift, void *buf, unsigned *words, int grid, SplitDev *out,
                               const uint32_t **count, hipStream_t s);
 // COO (idx_t 0 = int32, 1 = int64): flags gets VFLAG_BAD_FIRST for a row

@@ -1,15 +1,14 @@
 // Plan-time construction of the split gathers (SplitDev in spk_internal.h;
 // the product's kernels are in spk_spmv.h).
-//   k_split_count: every tile's entries per column block (an LDS histogram),
-//     counts[block][tile].
+//   k_split_count: every tile group's entries per column block (an LDS
+//     histogram), counts[block][group].
 //   k_split_scan_sums / _scan_tops / _scan: exclusive scan of the counts in
-//     that order, i.e. every segment's first stream position.
-//   k_split_fill: per tile, the segment table, then every entry's stream
-//     position (its column goes there) and its place in the tile's segments.
-//     Entries of one segment take their places in any order: the stream and
-//     perm agree, and the products sum in storage order.
-// Both walks over the entries read the column indices once: 2 x 4 bytes per
-// entry and 6 bytes written.
+//     that order, i.e. where a group's entries of a block begin in the stream.
+//   k_split_fill: per group and tile, every entry's stream position (its column
+//     goes there) and its place in the tile, in block order.
+// Entries of one block within a group, and within a tile, take their
+// positions and places in any order: cols, src and perm agree, and the
+// products sum in storage order.
 #include "spk_launch.h"
 #include "spk_spmv.h"
 
@@ -21,19 +20,29 @@ using namespace tile;
 
 constexpr int kScanItems = 4096;   // counts per workgroup of the scan (16 per thread)
 
+// f(entry range of every tile of the group that takes part).
+template <typename P, class F>
+__device__ __forceinline__ void group_tiles(int64_t n, const P *__restrict__ rp, int64_t group, F &&f) {
+    for (int t = 0; t < kSplitGroup; ++t) {
+        const int64_t r0 = (group * kSplitGroup + t) * kTileRows;
+        if (r0 >= n) break;
+        const int64_t s = static_cast<int64_t>(rp[r0]), e = static_cast<int64_t>(rp[min(r0 + kTileRows, n)]);
+        if (e > s && e - s <= kStreamCap) f(s, e);   // uniform
+    }
+}
+
 template <typename P, typename I>
 __global__ __launch_bounds__(kBlock) void k_split_count(int64_t n, const P *__restrict__ rp, const I *__restrict__ ci,
-                                                        int blocks, int shift, int64_t T, uint32_t *counts) {
+                                                        int blocks, int shift, int64_t groups, uint32_t *counts) {
     __shared__ uint32_t hist[kSplitBlocks];
-    for (int64_t tile = blockIdx.x; tile < T; tile += gridDim.x) {
-        const int64_t r0 = tile * kTileRows, r1 = min(r0 + kTileRows, n);
-        const int64_t s = static_cast<int64_t>(rp[r0]), e = static_cast<int64_t>(rp[r1]);
-        if (threadIdx.x < kSplitBlocks) hist[threadIdx.x] = 0;
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        for (int c = threadIdx.x; c < blocks; c += kBlock) hist[c] = 0;
         __syncthreads();
-        if (e - s <= kStreamCap)
+        group_tiles(n, rp, g, [&](int64_t s, int64_t e) {
             for (int64_t k = s + threadIdx.x; k < e; k += kBlock) atomicAdd(&hist[static_cast<int64_t>(ci[k]) >> shift], 1u);
+        });
         __syncthreads();
-        if (static_cast<int>(threadIdx.x) < blocks) counts[threadIdx.x * T + tile] = hist[threadIdx.x];
+        for (int c = threadIdx.x; c < blocks; c += kBlock) counts[c * groups + g] = hist[c];
         __syncthreads();
     }
 }
@@ -96,55 +105,73 @@ __global__ __launch_bounds__(kBlock) void k_split_scan(int64_t m, uint32_t *coun
     }
 }
 
-template <typename P, typename I>
+template <typename C, typename P, typename I>
 __global__ __launch_bounds__(kBlock) void k_split_fill(int64_t n, const P *__restrict__ rp, const I *__restrict__ ci,
-                                                       int blocks, int shift, int64_t T,
-                                                       const uint32_t *__restrict__ starts, int32_t *cols,
-                                                       uint16_t *perm, uint32_t *seg, uint16_t *off,
-                                                       const uint32_t *__restrict__ end) {
-    __shared__ uint32_t first[kSplitBlocks], place[kSplitBlocks], taken[kSplitBlocks];
-    for (int64_t tile = blockIdx.x; tile < T; tile += gridDim.x) {
-        const int64_t r0 = tile * kTileRows, r1 = min(r0 + kTileRows, n);
-        const int64_t s = static_cast<int64_t>(rp[r0]), e = static_cast<int64_t>(rp[r1]);
-        const int c = threadIdx.x;
-        uint32_t g = 0, len = 0, all;
-        if (c < blocks) {   // a thread per block
-            const int64_t at = static_cast<int64_t>(c) * T + tile;
-            g = starts[at];
-            len = (at + 1 < static_cast<int64_t>(blocks) * T ? starts[at + 1] : *end) - g;
-        }
-        const uint32_t inc = block_scan(len, &all);
-        if (c < kSplitBlocks) {
-            first[c] = g;
-            place[c] = inc - len;
-            taken[c] = 0;
-            if (c < blocks) {
-                seg[tile * blocks + c] = g;
-                off[tile * (blocks + 1) + c] = static_cast<uint16_t>(inc - len);
-                if (c == blocks - 1) off[tile * (blocks + 1) + blocks] = static_cast<uint16_t>(inc);
+                                                       int blocks, int shift, int64_t groups,
+                                                       const uint32_t *__restrict__ starts, C *cols,
+                                                       uint32_t *src, uint16_t *perm) {
+    __shared__ uint32_t next[kSplitBlocks], place[kSplitBlocks];
+    constexpr int U = kStreamCap / kBlock, B = kSplitBlocks / kBlock;
+    const int64_t within = sizeof(C) == 2 ? (int64_t(1) << shift) - 1 : -1;
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        for (int c = threadIdx.x; c < blocks; c += kBlock) next[c] = starts[c * groups + g];
+        group_tiles(n, rp, g, [&](int64_t s, int64_t e) {
+            for (int c = threadIdx.x; c < kSplitBlocks; c += kBlock) place[c] = 0;
+            __syncthreads();
+            int64_t col[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = s + threadIdx.x + u * kBlock;
+                col[u] = static_cast<int64_t>(ci[k < e ? k : e - 1]);
+                if (k < e) atomicAdd(&place[col[u] >> shift], 1u);
             }
-        }
-        __syncthreads();
-        if (e - s <= kStreamCap)
-            for (int64_t k = s + threadIdx.x; k < e; k += kBlock) {
-                const int64_t c = static_cast<int64_t>(ci[k]);
-                const int b = static_cast<int>(c >> shift);
-                const uint32_t r = atomicAdd(&taken[b], 1u);
-                cols[first[b] + r] = static_cast<int32_t>(c);
-                perm[k] = static_cast<uint16_t>(place[b] + r);
+            __syncthreads();
+            // exclusive scan over the blocks, B of them per thread
+            uint32_t own[B], sum = 0, all;
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                own[i] = place[threadIdx.x * B + i];
+                sum += own[i];
             }
+            uint32_t before = block_scan(sum, &all) - sum;
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                place[threadIdx.x * B + i] = before;
+                before += own[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = s + threadIdx.x + u * kBlock;
+                if (k >= e) continue;
+                const int c = static_cast<int>(col[u] >> shift);
+                const uint32_t at = atomicAdd(&next[c], 1u), p = atomicAdd(&place[c], 1u);
+                cols[at] = static_cast<C>(col[u] & within);
+                src[s + p] = at;
+                perm[k] = static_cast<uint16_t>(p);
+            }
+            __syncthreads();
+        });
         __syncthreads();
     }
+}
+
+// The blocks' first stream positions, and the end.
+__global__ __launch_bounds__(kBlock) void k_split_starts(int blocks, int64_t groups, const uint32_t *__restrict__ starts,
+                                                         const uint32_t *__restrict__ end, uint32_t *out) {
+    for (int c = threadIdx.x; c <= blocks; c += kBlock) out[c] = c < blocks ? starts[c * groups] : *end;
 }
 
 size_t up256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct Layout {
-    size_t xg, cols, perm, seg, off, rows, starts, sums, total;
+    size_t xg, cols, src, perm, start, rows, starts, sums, total;
 };
 
-Layout layout(int64_t n, int64_t nnz, int blocks) {
-    const size_t T = static_cast<size_t>((n + kTileRows - 1) / kTileRows), m = T * blocks;
+int64_t groups_of(int64_t n) { return (n + int64_t(kTileRows) * kSplitGroup - 1) / (int64_t(kTileRows) * kSplitGroup); }
+
+Layout layout(int64_t n, int64_t nnz, int blocks, int shift) {
+    const size_t m = static_cast<size_t>(groups_of(n)) * blocks;
     Layout l{};
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -153,10 +180,10 @@ Layout layout(int64_t n, int64_t nnz, int blocks) {
         return p;
     };
     l.xg = take(sizeof(double) * nnz);
-    l.cols = take(sizeof(int32_t) * nnz);
+    l.cols = take((shift <= kSplitLocal ? sizeof(uint16_t) : sizeof(int32_t)) * nnz);
+    l.src = take(sizeof(uint32_t) * nnz);
     l.perm = take(sizeof(uint16_t) * nnz);
-    l.seg = take(sizeof(uint32_t) * m);
-    l.off = take(sizeof(uint16_t) * T * (blocks + 1));
+    l.start = take(sizeof(uint32_t) * (blocks + 1));
     l.rows = take(rowpack_bytes(n));
     l.starts = take(sizeof(uint32_t) * m);
     l.sums = take(sizeof(uint32_t) * ((m + kScanItems - 1) / kScanItems + 1));
@@ -166,37 +193,47 @@ Layout layout(int64_t n, int64_t nnz, int blocks) {
 
 }  // namespace
 
-size_t split_buffer_bytes(int64_t n_rows, int64_t nnz, int blocks) { return layout(n_rows, nnz, blocks).total; }
+size_t split_buffer_bytes(int64_t n_rows, int64_t nnz, int blocks, int shift) {
+    return layout(n_rows, nnz, blocks, shift).total;
+}
 
 hipError_t launch_split_build(const CsrDev &A, int blocks, int shift, void *buf, unsigned *words, int grid, SplitDev *out,
                               const uint32_t **count, hipStream_t s) {
     if (blocks < 1 || blocks > kSplitBlocks || shift < 0 || A.nnz > INT32_MAX || A.n_rows < 1 ||
         ((A.n_cols - 1) >> shift) >= blocks)
         return hipErrorInvalidValue;
-    const Layout l = layout(A.n_rows, A.nnz, blocks);
+    const Layout l = layout(A.n_rows, A.nnz, blocks, shift);
     char *p = static_cast<char *>(buf);
-    const int64_t T = (A.n_rows + kTileRows - 1) / kTileRows, m = T * blocks;
+    const int64_t groups = groups_of(A.n_rows), m = groups * blocks;
     const int nb = static_cast<int>((m + kScanItems - 1) / kScanItems);
     uint32_t *starts = reinterpret_cast<uint32_t *>(p + l.starts), *sums = reinterpret_cast<uint32_t *>(p + l.sums);
+    uint32_t *src = reinterpret_cast<uint32_t *>(p + l.src), *start = reinterpret_cast<uint32_t *>(p + l.start);
+    uint16_t *perm = reinterpret_cast<uint16_t *>(p + l.perm);
     SplitDev d;
     d.xg = p + l.xg;
-    d.cols = reinterpret_cast<int32_t *>(p + l.cols);
-    d.perm = reinterpret_cast<uint16_t *>(p + l.perm);
-    d.seg = reinterpret_cast<uint32_t *>(p + l.seg);
-    d.off = reinterpret_cast<uint16_t *>(p + l.off);
+    d.cols = p + l.cols;
+    d.src = src;
+    d.perm = perm;
+    d.start = start;
     d.rows = p + l.rows;
     d.blocks = blocks;
     d.shift = shift;
     const hipError_t e = dispatch_idx(A, [&](auto rp, auto ci) {
         using P = pointee_t<decltype(rp)>;
         using I = pointee_t<decltype(ci)>;
-        hipLaunchKernelGGL((k_split_count<P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, ci, blocks, shift, T, starts);
+        hipLaunchKernelGGL((k_split_count<P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, ci, blocks, shift, groups,
+                           starts);
         hipLaunchKernelGGL(k_split_scan_sums, dim3(nb), dim3(kBlock), 0, s, m, starts, sums);
         hipLaunchKernelGGL(k_split_scan_tops, dim3(1), dim3(kBlock), 0, s, nb, sums);
         hipLaunchKernelGGL(k_split_scan, dim3(nb), dim3(kBlock), 0, s, m, starts, sums);
-        hipLaunchKernelGGL((k_split_fill<P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, ci, blocks, shift, T, starts,
-                           const_cast<int32_t *>(d.cols), const_cast<uint16_t *>(d.perm), const_cast<uint32_t *>(d.seg),
-                           const_cast<uint16_t *>(d.off), sums + nb);
+        hipLaunchKernelGGL(k_split_starts, dim3(1), dim3(kBlock), 0, s, blocks, groups, starts, sums + nb, start);
+        auto fill = [&](auto cols) {
+            using C = std::remove_pointer_t<decltype(cols)>;
+            hipLaunchKernelGGL((k_split_fill<C, P, I>), dim3(grid), dim3(kBlock), 0, s, A.n_rows, rp, ci, blocks, shift,
+                               groups, starts, cols, src, perm);
+        };
+        if (shift <= kSplitLocal) fill(reinterpret_cast<uint16_t *>(p + l.cols));
+        else fill(reinterpret_cast<int32_t *>(p + l.cols));
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;

@@ -492,14 +492,18 @@ k_spmv_pattern(int64_t n, int64_t nnz, const RowPack *__restrict__ rp, const uin
 // columns nearly every 8-byte read brings a 128-byte line through the fabric
 // (8.4 GB per product of 7e7 entries), at 1e6 from the L2 (170e9 reads/s).
 // Taken block by block of 2^shift columns, the gathers find their slice of x
-// in LDS (blocks of 128 KB) or in the XCD's L2 (larger ones); what is added
-// is streamed: 4 bytes of column and 8 of value per entry out of the first
-// launch, 8 of value and 2 of place into the second.  Row sums run in storage
-// order on the caller's values, so products equal the plain ones bit for bit.
-// Random pattern, 7 entries per row, us per product, plain / split (the two
-// launches): FP64 n = 1e6 68 / 52 (20 + 32), n = 2e6 180 / 110, n = 1e7
-// 1,170 / 772 (474 + 322 under the profiler; the L2 gathers are bound by the
-// misses a CU keeps in flight); FP32 n = 3e6 228 / 119 (35 + 84).
+// in LDS (blocks of 128 KB) or in the XCD's L2 (larger ones, past 1,024 such
+// blocks); what is added is streamed: 2 bytes of local column and 8 of value
+// per entry out of the first launch, 8 of value, 4 of position and 2 of place
+// into the second.  A tile reads its values in block order, so that the runs
+// of one block (some 3 of a tile's 1,792 entries at 611 blocks, 12 of a group
+// of four tiles') share lines: 1.9 GB fetched where 1.5 are needed, at 4.4
+// TB/s.  Groups of 2, 8 and 16 tiles measure the same.  Row sums run in
+// storage order on the caller's values, so products equal the plain ones bit
+// for bit.  Random pattern, 7 entries per row, us per call, plain / split (the
+// two launches): FP64 n = 1e6 68 / 58 (17 + 32), n = 2e6 180 / 98, n = 1e7
+// 1,186 / 587 (145 + 430; with the slices of 128 blocks gathered from L2,
+// 795: 474 + 322); FP32 n = 3e6 228 / 102.
 constexpr int kSplitDepth = 8;   // gathers in flight per thread
 
 template <typename X, class Epi>
@@ -529,8 +533,7 @@ __global__ __launch_bounds__(kBlock) void k_split_gather(const int32_t *__restri
 }
 
 // The same with the block's slice of x in LDS: a workgroup loads it and takes
-// its part (of `parts`) of the block's stream.  start[c]: block c's first
-// stream position (seg of tile 0).
+// its part (of `parts`) of the block's stream.
 constexpr int kSplitLdsThreads = 1024;
 constexpr size_t kSplitLds = size_t(128) << 10;
 
@@ -542,7 +545,7 @@ __global__ __launch_bounds__(kSplitLdsThreads) void k_split_gather_lds(SplitDev 
     const int c = blockIdx.x / parts, part = blockIdx.x % parts;
     const int64_t first = static_cast<int64_t>(c) << sp.shift;
     const int width = static_cast<int>(min(n_cols - first, static_cast<int64_t>(1) << sp.shift));
-    const int64_t b0 = sp.seg[c], b1 = c + 1 < sp.blocks ? static_cast<int64_t>(sp.seg[c + 1]) : sp.count;
+    const int64_t b0 = sp.start[c], b1 = sp.start[c + 1];
     const int64_t j0 = b0 + (b1 - b0) * part / parts, j1 = b0 + (b1 - b0) * (part + 1) / parts;
     const X *xs = x + first;
     constexpr int U = 8;
@@ -555,38 +558,39 @@ __global__ __launch_bounds__(kSplitLdsThreads) void k_split_gather_lds(SplitDev 
             if (i + u * kSplitLdsThreads < width) lx[i + u * kSplitLdsThreads] = v[u];
     }
     __syncthreads();
+    // 16 bytes of values per thread and store: W places of the stream at a
+    // time, aligned (those of a neighbouring part are left to it); a place at
+    // a time n = 1e7 takes 201 us, so 145
+    constexpr int W = 16 / sizeof(X), D = 16 / W;
+    using KV = uint16_t __attribute__((ext_vector_type(W)));
+    using XV = X __attribute__((ext_vector_type(W)));
     X *xg = static_cast<X *>(sp.xg);
-    for (int64_t base = j0 + threadIdx.x; base < j1; base += U * kSplitLdsThreads) {
-        int32_t k[U];
+    const KV *cols = static_cast<const KV *>(sp.cols);
+    const int64_t w1 = (j1 + W - 1) / W;
+    for (int64_t base = j0 / W + threadIdx.x; base < w1; base += D * kSplitLdsThreads) {
+        KV k[D];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t j = base + u * kSplitLdsThreads;
-            k[u] = sp.cols[j < j1 ? j : j1 - 1] - static_cast<int32_t>(first);
+        for (int u = 0; u < D; ++u) {
+            const int64_t w = base + u * kSplitLdsThreads;
+            k[u] = cols[w < w1 ? w : w1 - 1];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t j = base + u * kSplitLdsThreads;
-            if (j < j1) xg[j] = lx[k[u]];
+        for (int u = 0; u < D; ++u) {
+            const int64_t w = base + u * kSplitLdsThreads, j = w * W;
+            if (w >= w1) continue;
+            if (j >= j0 && j + W <= j1) {
+                XV v;
+#pragma unroll
+                for (int i = 0; i < W; ++i) v[i] = lx[k[u][i]];
+                reinterpret_cast<XV *>(xg)[w] = v;
+            } else {
+#pragma unroll
+                for (int i = 0; i < W; ++i)
+                    if (j + i >= j0 && j + i < j1) xg[j + i] = lx[k[u][i]];
+            }
         }
     }
 }
-
-// One tile's segment table, up to two blocks per lane.
-struct SplitMeta {
-    uint32_t seg[2];
-    uint16_t a[2], b[2];
-    __device__ __forceinline__ void load(const SplitDev &sp, int64_t tile) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = (threadIdx.x & 63) + 64 * h;
-            const int c = i < sp.blocks ? i : sp.blocks - 1;
-            seg[h] = sp.seg[tile * sp.blocks + c];
-            const uint16_t *o = sp.off + tile * (sp.blocks + 1) + c;
-            a[h] = o[0];
-            b[h] = o[1];
-        }
-    }
-};
 
 // The row tiles of a product whose gathers have run.  Tiles of more than
 // kStreamCap entries gather from x themselves (ci: the plain indices, 64-bit
@@ -607,14 +611,11 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
     __shared__ X lx[kStreamCap];
     const RowPack *rp = static_cast<const RowPack *>(sp.rows);
     const X *xg = static_cast<const X *>(sp.xg);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t T = (n + kTileRows - 1) / kTileRows;
     TileIter it(T, remap, W);
     if (it.valid()) {
         TileMeta<RowPack> cur, nxt;
-        SplitMeta sc, sn;
         cur.load(rp, n, it.tile());
-        sc.load(sp, it.tile());
         while (true) {
             TileIter after = it;
             after.next();
@@ -626,24 +627,26 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
             if (e - s <= kStreamCap) {
                 dma_chunks<V>(va, s, e, nnz, lv, nt);
                 dma_chunks<uint16_t>(sp.perm, s, e, nnz, lp, nt);
-                // the segments, a wave each in turn, 4 bytes per lane
-                auto segment = [&](uint32_t g, int at, int end) {
-                    const int words = (end - at) * static_cast<int>(sizeof(X) / 4);
-                    const uint32_t *src = reinterpret_cast<const uint32_t *>(xg + g);
-                    uint32_t *dst = reinterpret_cast<uint32_t *>(lx + at);
-                    for (int q = 0; q < words; q += 64)
-                        if (q + lane < words)
-                            __builtin_amdgcn_global_load_lds(static_cast<const void *>(src + q + lane),
-                                                             (lds_void *)(dst + q), 4, 0, 0);
-                };
+                // the tile's values of x: both rounds of loads whole before
+                // the first use (places past the end re-read the last one)
+                constexpr int U = kStreamCap / kBlock;
+                const int m = static_cast<int>(e - s);
+                uint32_t at[U];
+                X xv[U];
+                if (m > 0) {   // uniform
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    for (int c = wid; c < min(64, sp.blocks - 64 * h); c += kBlock / 64)
-                        segment(__builtin_amdgcn_readlane(sc.seg[h], c), __builtin_amdgcn_readlane(static_cast<int>(sc.a[h]), c),
-                                __builtin_amdgcn_readlane(static_cast<int>(sc.b[h]), c));
-                if (more) {
-                    nxt.load(rp, n, after.tile());
-                    sn.load(sp, after.tile());
+                    for (int u = 0; u < U; ++u) {
+                        const int p = threadIdx.x + u * kBlock;
+                        at[u] = __builtin_nontemporal_load(sp.src + s + (p < m ? p : m - 1));
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) xv[u] = xg[at[u]];
+                }
+                if (more) nxt.load(rp, n, after.tile());
+                if (m > 0) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (static_cast<int>(threadIdx.x) + u * kBlock < m) lx[threadIdx.x + u * kBlock] = xv[u];
                 }
                 const auto pv = pre_of(epi, row < r1 ? row : r1 - 1);
                 __builtin_amdgcn_s_waitcnt(0);   // this wave's DMA has landed
@@ -660,10 +663,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
                 __builtin_amdgcn_s_setprio(0);
                 lds_barrier();
             } else {
-                if (more) {
-                    nxt.load(rp, n, after.tile());
-                    sn.load(sp, after.tile());
-                }
+                if (more) nxt.load(rp, n, after.tile());
                 const PlainGather<X, C> gx{x};
                 if (row < r1 && lra.base && b - a > kLongRow)   // its pieces have been summed
                     epi.row(row, lra.template sum<C>(row, b - a));
@@ -676,10 +676,16 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
             if (!more) break;
             it = after;
             cur = nxt;
-            sc = sn;
         }
     }
     epi.finish();
+}
+
+// Parts of a block's stream in k_split_gather_lds, one workgroup and slice load
+// each: about one workgroup per CU for few blocks, two parts when the blocks
+// alone are one to four per CU (their last round is then half as long).
+inline int split_parts(int cus, int blocks) {
+    return blocks <= cus ? std::max(1, cus / blocks) : blocks < 4 * cus ? 2 : 1;
 }
 
 template <class F>
@@ -710,7 +716,10 @@ template <typename V, typename X, typename C, class Epi>
 hipError_t launch_family(const CsrDev &A, const SpmvTune &t, const X *x, const Epi &epi, hipStream_t s) {
     if (A.n_rows == 0) return hipSuccess;
     if constexpr (!HasGather<Epi>::value) {
-        if (t.kind == 0 && t.split && A.split.xg && (reinterpret_cast<uintptr_t>(A.va) & 15) == 0) {
+        // local columns want their block's slice in LDS: not split where X is too wide for that
+        const bool local = A.split.shift <= kSplitLocal;
+        if (t.kind == 0 && t.split && A.split.xg && (reinterpret_cast<uintptr_t>(A.va) & 15) == 0 &&
+            (!local || (sizeof(X) << A.split.shift) <= kSplitLds)) {
             constexpr auto K = k_spmv_split<V, X, C, Epi>;
             const int per_cu = resident_per_cu<K>();
             const int walk = t.cus > 0 && per_cu > 0 ? std::min(t.grid, t.cus * per_cu) : 0;
@@ -723,13 +732,14 @@ hipError_t launch_family(const CsrDev &A, const SpmvTune &t, const X *x, const E
                 if (A.idx_t == 0) pieces(static_cast<const int32_t *>(A.ci));
                 else pieces(static_cast<const int64_t *>(A.ci));
             }
-            if (A.split.count > 0 && (sizeof(X) << A.split.shift) <= kSplitLds)
+            if (A.split.count > 0 && local)
                 hipLaunchKernelGGL((k_split_gather_lds<X, Epi>),
-                                   dim3(A.split.blocks * std::max(1, t.cus / A.split.blocks)), dim3(kSplitLdsThreads), 0, s,
-                                   A.split, std::max(1, t.cus / A.split.blocks), A.n_cols, x, epi);
+                                   dim3(A.split.blocks * split_parts(t.cus, A.split.blocks)), dim3(kSplitLdsThreads), 0, s,
+                                   A.split, split_parts(t.cus, A.split.blocks), A.n_cols, x, epi);
             else if (A.split.count > 0)
                 hipLaunchKernelGGL((k_split_gather<X, Epi>), dim3(t.cus > 0 ? std::min(t.cus * 8, kMaxGrid) : t.grid),
-                                   dim3(kBlock), 0, s, A.split.cols, A.split.count, x, static_cast<X *>(A.split.xg), epi);
+                                   dim3(kBlock), 0, s, static_cast<const int32_t *>(A.split.cols), A.split.count, x,
+                                   static_cast<X *>(A.split.xg), epi);
             hipLaunchKernelGGL(K, dim3(t.grid), dim3(kBlock), 0, s, A.n_rows, A.nnz, A.ci, A.idx_t, static_cast<const V *>(A.va),
                                x, A.split, t.xcd_remap, t.nt, walk, epi,
                                LongArg<2>{A.pieces ? A.long_base : nullptr, A.piece_sums});

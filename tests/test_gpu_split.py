@@ -46,7 +46,8 @@ MATS = {
     "randsym_40000": lambda: inputs.randsym(40000, 2),
     "hubs_60000": lambda: inputs.powerlaw(60000, 3),
     "ragged": lambda: ragged(3001, 50001, 14, 4),
-    "wide": lambda: ragged(700, 2200001, 14, 5),          # 135 blocks of 2^14 columns: past the FP64 LDS blocks
+    "wide": lambda: ragged(700, 2200001, 14, 5),          # 135 blocks of 2^14 columns
+    "wider": lambda: ragged(700, 16800001, 14, 7),        # 1,026 of them: past the FP64 LDS blocks
     "dense_tiles": lambda: ragged(1500, 20000, 40, 6),    # most tiles past 2,048 entries
     "one_row": lambda: ragged(1, 10, 9, 9),
 }
@@ -102,6 +103,28 @@ def test_solves(spk, ctx, monkeypatch, solver, precision):
     # kappa <= 18.3 (Gershgorin) and tau = 1e-12
     assert rel(out[0], xo) <= 1e-10
     assert np.array_equal(out[0].view(np.uint64), out[1].view(np.uint64))
+
+
+def test_solve_of_fp32_values(spk, ctx, monkeypatch):
+    """FP32 values: FP32 vectors in the inner loop, FP64 ones in the outer
+    residuals; the blocks of one plan serve both."""
+    A = inputs.randsym(150000, 2)
+    A = inputs.CSR(A.n_rows, A.n_cols, A.row_ptr, A.col, A.val.astype(np.float32).astype(np.float64))
+    bh = inputs.rhs(A.n_rows, 2)
+    cfg = spk.spk_solver_cfg_default()
+    cfg.solver = spk.SOLVER_CG
+    cfg.precision = spk.PREC_MIXED_FP32
+    cfg.reduction_factor = 1e-12
+    monkeypatch.setenv("SPK_SPLIT", "1")
+    monkeypatch.setenv("SPK_SPMV_KERNEL", "stream,split=1,remap=64,nt=1")
+    pl = spk.spk_plan_solve(ctx, dev_csr(spk, A, val=torch.float32), cfg)
+    x = torch.zeros(A.n_rows, dtype=torch.float64, device=DEV)
+    log = spk.spk_execute_solve(pl, to_dev(bh), x)
+    spk.spk_free(pl)
+    assert log.stop_reason == spk.STOP_CONVERGED
+    xo, _, _ = oracle.cg(A, bh, tau=1e-14, max_iters=1000)
+    # kappa <= 18.3 (Gershgorin) and tau = 1e-12
+    assert rel(x.cpu().numpy(), xo) <= 1e-10
 
 
 def test_unaligned_values(spk, ctx, monkeypatch):
