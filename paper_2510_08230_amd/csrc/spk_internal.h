@@ -123,6 +123,15 @@ struct PersistSolve {
     int remap, nt, true_residual;
 };
 
+// Whether the vectors of a CG loop (x, p, r and q of n values of T) outgrow the
+// 256 MB Infinity Cache, and the passes over them go past it with those that
+// they do not share (k_cg_pupdate).  Plain / past it, us per FP64 solve: 45 MB
+// per vector 5,940 / 5,985, 64 MB 8,180 / 7,980.
+template <typename T>
+constexpr bool stream_vectors(int64_t n) {
+    return n >= (int64_t(60) << 20) / static_cast<int64_t>(sizeof(T));
+}
+
 // Restarted GMRES: the small per-solve arrays (device memory, one per plan).
 constexpr int kMaxKrylov = 32;   // largest restart length m
 struct GmresState {

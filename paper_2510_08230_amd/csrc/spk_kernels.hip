@@ -226,7 +226,8 @@ __global__ __launch_bounds__(kBlock) void k_init_finish(SolveState *st, const do
 // r -= alpha q with alpha = rho_k / (p . q) (FP64 scalar, applied in T);
 // partials of r.r accumulated in FP64.  x += alpha p is left to the p-update
 // kernel, which reads p anyway.  j: index of this iteration within the chunk.
-template <typename T>
+// Stream: q is not read again (stream_vectors).
+template <typename T, bool Stream>
 __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, T *__restrict__ r, const T *__restrict__ q,
                                                       SolveState *st, const double *part_pq, int G_pq,
                                                       double *part_rr, int j) {
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, T *__restrict__
     const VT *qv_ = reinterpret_cast<const VT *>(q);
     for (int64_t i = gid; i < nv; i += stride) {
         VT rv = rv_[i];
-        const VT qv = qv_[i];
+        const VT qv = Stream ? __builtin_nontemporal_load(qv_ + i) : qv_[i];
 #pragma unroll
         for (int c = 0; c < W; ++c) {
             rv[c] = fma(-alpha, qv[c], rv[c]);
@@ -279,7 +280,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, T *__restrict__
 // stop test on rho_{k+1} = r.r (partials of the update kernel), beta =
 // rho_{k+1} / rho_k and, unless stopping, p = r + beta p.  One pass over
 // x, p and r.
-template <typename T>
+//
+// Bound by bytes: 40 of the loop's 64 vector bytes per unknown and iteration.
+// Stream: the loop's vectors outgrow the Infinity Cache (stream_vectors).  x,
+// which nothing else reads, goes past it, and a thread walks backwards, from
+// the part of r that the update has just written to the part of p that the
+// next product reads first; so p, r and q keep their lines.  us per solve,
+// without / with (x alone; and q; and backwards): FP64 n = 200^3 8,180 /
+// 7,980, 215^3 10,690 / 10,150 (10,240; 10,155), 240^3 14,980 / 13,850, 300^3
+// 30,350 / 28,720 (29,190 forwards); FP32 loop n = 256^3 9,520 / 9,075.
+template <typename T, bool Stream>
 __global__ __launch_bounds__(kBlock) void k_cg_pupdate(int64_t n, const T *__restrict__ r, T *__restrict__ p,
                                                        SolveState *st, const double *part_rr, int G_rr, int j) {
     if (st->stop != STOP_RUNNING) return;   // breakdown in the update: x keeps x_k
@@ -316,16 +326,23 @@ __global__ __launch_bounds__(kBlock) void k_cg_pupdate(int64_t n, const T *__res
         VT *pv_ = reinterpret_cast<VT *>(p);
         const VT *rv_ = reinterpret_cast<const VT *>(r);
         if (more) {
-            for (int64_t i = gid; i < nv; i += stride) {
-                VT xv = xv_[i], pv = pv_[i];
+            auto pass = [&](int64_t i) {
+                VT xv = Stream ? __builtin_nontemporal_load(xv_ + i) : xv_[i], pv = pv_[i];
                 const VT rv = rv_[i];
 #pragma unroll
                 for (int c = 0; c < W; ++c) {
                     xv[c] = fma(alpha, pv[c], xv[c]);
                     pv[c] = fma(beta, pv[c], rv[c]);
                 }
-                xv_[i] = xv;
+                if constexpr (Stream) __builtin_nontemporal_store(xv, xv_ + i);
+                else xv_[i] = xv;
                 pv_[i] = pv;
+            };
+            if constexpr (Stream) {
+                if (gid < nv)
+                    for (int64_t i = gid + (nv - 1 - gid) / stride * stride; i >= 0; i -= stride) pass(i);
+            } else {
+                for (int64_t i = gid; i < nv; i += stride) pass(i);
             }
         } else {
             for (int64_t i = gid; i < nv; i += stride) {
@@ -1370,32 +1387,41 @@ hipError_t launch_cg_spmv_pq32(const CsrDev &A32, const SpmvTune &t, const float
     return hipErrorInvalidValue;
 }
 
+template <typename T>
+static hipError_t cg_update(int64_t n, int grid, int spmv_grid, int j, T *r, const T *q, SolveState *st,
+                            double *partials, hipStream_t s) {
+    const auto K = stream_vectors<T>(n) ? k_cg_update<T, true> : k_cg_update<T, false>;
+    hipLaunchKernelGGL(K, dim3(grid), dim3(kBlock), 0, s, n, r, q, st, site(partials, SITE_PQ), spmv_grid,
+                       site(partials, SITE_RR), j);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t cg_pupdate(int64_t n, int grid, int j, const T *r, T *p, SolveState *st, double *partials,
+                             hipStream_t s) {
+    const auto K = stream_vectors<T>(n) ? k_cg_pupdate<T, true> : k_cg_pupdate<T, false>;
+    hipLaunchKernelGGL(K, dim3(grid), dim3(kBlock), 0, s, n, r, p, st, site(partials, SITE_RR), grid, j);
+    return hipGetLastError();
+}
+
 hipError_t launch_cg_update(int64_t n, int grid, int spmv_grid, int j, double *r, const double *q, SolveState *st,
                             double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_update<double>, dim3(grid), dim3(kBlock), 0, s, n, r, q, st, site(partials, SITE_PQ),
-                       spmv_grid, site(partials, SITE_RR), j);
-    return hipGetLastError();
+    return cg_update(n, grid, spmv_grid, j, r, q, st, partials, s);
 }
 
 hipError_t launch_cg_update32(int64_t n, int grid, int spmv_grid, int j, float *r, const float *q, SolveState *st,
                               double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_update<float>, dim3(grid), dim3(kBlock), 0, s, n, r, q, st, site(partials, SITE_PQ),
-                       spmv_grid, site(partials, SITE_RR), j);
-    return hipGetLastError();
+    return cg_update(n, grid, spmv_grid, j, r, q, st, partials, s);
 }
 
 hipError_t launch_cg_pupdate(int64_t n, int grid, int j, const double *r, double *p, SolveState *st, double *partials,
                              hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_pupdate<double>, dim3(grid), dim3(kBlock), 0, s, n, r, p, st, site(partials, SITE_RR),
-                       grid, j);
-    return hipGetLastError();
+    return cg_pupdate(n, grid, j, r, p, st, partials, s);
 }
 
 hipError_t launch_cg_pupdate32(int64_t n, int grid, int j, const float *r, float *p, SolveState *st,
                                double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_pupdate<float>, dim3(grid), dim3(kBlock), 0, s, n, r, p, st, site(partials, SITE_RR),
-                       grid, j);
-    return hipGetLastError();
+    return cg_pupdate(n, grid, j, r, p, st, partials, s);
 }
 
 hipError_t launch_ir_residual(const CsrDev &A, const SpmvTune &t, const double *b, const double *x, float *r32,

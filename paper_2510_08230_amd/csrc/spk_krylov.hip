@@ -331,6 +331,8 @@ __global__ __launch_bounds__(kBlock) void k_pcg_init_finish(SolveState *st, cons
 }
 
 // alpha = rho_k / p.q; r -= alpha q; partials of r.r and r.z (z = dinv r).
+// Stream: as in the CG loop (stream_vectors).
+template <bool Stream>
 __global__ __launch_bounds__(kBlock) void k_pcg_update(int64_t n, double *__restrict__ r, const double *__restrict__ q,
                                                        const double *__restrict__ dinv, SolveState *st,
                                                        const double *part_pq, int G_pq, double *part_rr, int j) {
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update(int64_t n, double *__rest
     const V2 *dv = reinterpret_cast<const V2 *>(dinv);
     for (int64_t i = gid; i < nv; i += stride) {
         V2 ri = rv[i];
-        const V2 qi = qv[i], di = dv[i];
+        const V2 qi = Stream ? __builtin_nontemporal_load(qv + i) : qv[i], di = dv[i];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             ri[c] = fma(-alpha, qi[c], ri[c]);
@@ -381,6 +383,8 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update(int64_t n, double *__rest
 }
 
 // x += alpha p; stop test on ||r_{k+1}||; rho_{k+1} = r.z; beta; p = z + beta p.
+// Stream: x past the caches and the walk backwards, as in the CG loop.
+template <bool Stream>
 __global__ __launch_bounds__(kBlock) void k_pcg_pupdate(int64_t n, const double *__restrict__ r,
                                                         const double *__restrict__ dinv, double *__restrict__ p,
                                                         SolveState *st, const double *part_rr, int G_rr, int j) {
@@ -416,17 +420,24 @@ __global__ __launch_bounds__(kBlock) void k_pcg_pupdate(int64_t n, const double 
         V2 *pv = reinterpret_cast<V2 *>(p);
         const V2 *rv = reinterpret_cast<const V2 *>(r);
         const V2 *dv = reinterpret_cast<const V2 *>(dinv);
-        for (int64_t i = gid; i < nv; i += stride) {
-            V2 xi = xv[i], pi = pv[i];
+        auto pass = [&](int64_t i) {
+            V2 xi = Stream ? __builtin_nontemporal_load(xv + i) : xv[i], pi = pv[i];
 #pragma unroll
             for (int c = 0; c < 2; ++c) xi[c] = fma(alpha, pi[c], xi[c]);
-            xv[i] = xi;
+            if constexpr (Stream) __builtin_nontemporal_store(xi, xv + i);
+            else xv[i] = xi;
             if (more) {
                 const V2 ri = rv[i], di = dv[i];
 #pragma unroll
                 for (int c = 0; c < 2; ++c) pi[c] = fma(beta, pi[c], ri[c] * di[c]);
                 pv[i] = pi;
             }
+        };
+        if constexpr (Stream) {
+            if (gid < nv)
+                for (int64_t i = gid + (nv - 1 - gid) / stride * stride; i >= 0; i -= stride) pass(i);
+        } else {
+            for (int64_t i = gid; i < nv; i += stride) pass(i);
         }
         done = nv * 2;
     }
@@ -514,14 +525,16 @@ hipError_t launch_pcg_init(const CsrDev &A, const SpmvTune &t, const double *b, 
 
 hipError_t launch_pcg_update(int64_t n, int grid, int spmv_grid, int j, double *r, const double *q,
                              const double *dinv, SolveState *st, double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_pcg_update, dim3(grid), dim3(kBlock), 0, s, n, r, q, dinv, st, site(partials, SITE_PQ),
+    const auto K = stream_vectors<double>(n) ? k_pcg_update<true> : k_pcg_update<false>;
+    hipLaunchKernelGGL(K, dim3(grid), dim3(kBlock), 0, s, n, r, q, dinv, st, site(partials, SITE_PQ),
                        spmv_grid, site(partials, SITE_RR), j);
     return hipGetLastError();
 }
 
 hipError_t launch_pcg_pupdate(int64_t n, int grid, int j, const double *r, const double *dinv, double *p,
                               SolveState *st, double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_pcg_pupdate, dim3(grid), dim3(kBlock), 0, s, n, r, dinv, p, st, site(partials, SITE_RR),
+    const auto K = stream_vectors<double>(n) ? k_pcg_pupdate<true> : k_pcg_pupdate<false>;
+    hipLaunchKernelGGL(K, dim3(grid), dim3(kBlock), 0, s, n, r, dinv, p, st, site(partials, SITE_RR),
                        grid, j);
     return hipGetLastError();
 }
