@@ -303,12 +303,12 @@ spk_status spk_free(spk_plan plan);
  * launch shape is one an earlier plan of the same shape tuned on this
  * context (never tuned here), else the heuristic one, so a solve after such
  * a plan runs the same kernels and gives the same result (for matrices of
- * fewer than 2^22 entries: larger plans also derive column codes, which this
- * solve does not, so its launch shape and rounding can differ there).  Every call on one
- * GPU shares that GPU's scratch, which keeps the last call's contents (the
- * call clears what must start at zero): calls that overlap on one GPU, from
- * any context or stream, race and must not be issued.  Synchronises the
- * context stream before returning.
+ * fewer than 2^22 entries: larger plans also derive column codes or split
+ * their gathers, which this solve does not, so its launch shape and rounding
+ * can differ there).  Every call on one GPU shares that GPU's scratch, which
+ * keeps the last call's contents (the call clears what must start at zero):
+ * calls that overlap on one GPU, from any context or stream, race and must
+ * not be issued.  Synchronises the context stream before returning.
  * Errors: INVALID_ARG (malformed or non-square A, too many rows, null
  * vectors), UNSUPPORTED (other configurations), DEVICE. */
 spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *cfg, const void *b, void *x,

@@ -565,8 +565,9 @@ spk_status build_patterns(spk_plan pl) {
 
 // The split of A's gathers, where split_shift allows one and the tuner has not
 // already timed this shape and found it slower.  vt: the value type of the
-// products that are tuned.  Without memory for it the products gather as they
-// go.
+// products that are tuned.  It must leave as much again and the solve's
+// vectors free (up to 64 with a GMRES basis); without that, or without memory
+// for it, the products gather as they go.
 spk_status build_split(spk_plan pl, int use, int vt) {
     spk_ctx ctx = pl->ctx;
     CsrDev &A = pl->A;
@@ -580,8 +581,12 @@ spk_status build_split(spk_plan pl, int use, int vt) {
     const auto hit = ctx->tune_cache.find(tune_key(probe, use));
     if (hit != ctx->tune_cache.end() && !hit->second.tune.split) return SPK_OK;
     const int blocks = static_cast<int>((A.n_cols - 1) >> shift) + 1;
+    const size_t bytes = spk::split_buffer_bytes(A.n_rows, A.nnz, blocks, shift);
+    size_t avail = 0, total_mem = 0;
+    SPK_HIP(ctx, hipMemGetInfo(&avail, &total_mem));
+    if (avail < 2 * bytes + 64 * sizeof(double) * static_cast<size_t>(A.n_rows)) return SPK_OK;
     void *buf = nullptr;
-    if (ctx->dpool.get(spk::split_buffer_bytes(A.n_rows, A.nnz, blocks, shift), &buf) != hipSuccess) return SPK_OK;
+    if (ctx->dpool.get(bytes, &buf) != hipSuccess) return SPK_OK;
     spk::SplitDev d;
     const uint32_t *count = nullptr;
     unsigned *words = reinterpret_cast<unsigned *>(ctx->d_probe + spk::kCodeSlots);
@@ -1532,10 +1537,10 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         const size_t cb = kResidentCtlBytes;
         if (!dget(cb, &pl->res_ctl) || !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch) ||
             (mixed && !dget(sizeof(spk::PersistResult), &pl->persist_res)))
-            return cleanup(SPK_ERR_OUT_OF_MEMORY, "resident solve workspace");
-        if (hipMemsetAsync(pl->res_ctl, 0, cb, ctx->stream) != hipSuccess ||
-            hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess ||
-            (mixed && hipMemsetAsync(pl->persist_res, 0, sizeof(spk::PersistResult), ctx->stream) != hipSuccess))
+            pl->res_grid = 0;   // no memory for it: the loop
+        else if (hipMemsetAsync(pl->res_ctl, 0, cb, ctx->stream) != hipSuccess ||
+                 hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess ||
+                 (mixed && hipMemsetAsync(pl->persist_res, 0, sizeof(spk::PersistResult), ctx->stream) != hipSuccess))
             return cleanup(SPK_ERR_DEVICE, "resident solve workspace");
     }
     int mode = cfg.exec_mode;
