@@ -309,9 +309,9 @@ hipError_t launch_narrow_i32(int64_t count, const int64_t *src, int32_t *dst, in
 hipError_t launch_batch_tick(const BatchDev &B, hipStream_t s) {
     hipLaunchKernelGGL(k_b_spmv, dim3(B.tile_grid), dim3(kBlock), 0, s, B);
     hipLaunchKernelGGL(k_b_reduce_a, dim3(B.slot_grid), dim3(kBlock), 0, s, B);
-    hipLaunchKernelGGL(k_b_update, dim3(B.tile_grid), dim3(kBlock), 0, s, B);
+    hipLaunchKernelGGL(k_b_update, dim3(B.vec_grid), dim3(kBlock), 0, s, B);
     hipLaunchKernelGGL(k_b_reduce_b, dim3(B.slot_grid), dim3(kBlock), 0, s, B);
-    hipLaunchKernelGGL(k_b_pupdate, dim3(B.tile_grid), dim3(kBlock), 0, s, B);
+    hipLaunchKernelGGL(k_b_pupdate, dim3(B.vec_grid), dim3(kBlock), 0, s, B);
     hipLaunchKernelGGL(k_b_commit, dim3(1), dim3(kBlock), 0, s, B);
     return hipGetLastError();
 }

@@ -311,6 +311,14 @@ struct SlotStatus {
     double rnorm, bnorm;
 };
 
+// Workgroups per CU of the tick's vector launches: all that a CU holds, since a
+// tile's few loads wait behind those of its table entry, descriptor and state.
+// 64 requests of 1e3 to 1e6 rows, us per tick and ms in all, with the four of
+// the product's launch / with eight: update 87 / 54, p 30 / 20, 29.3 / 27.0 ms
+// (sixteen 26.9).  The product keeps its own figure: 5 or 6 per CU gather
+// through the same L2s in 434 us, 4 in 339.
+constexpr int kTickVecBlocks = 8;
+
 // Device tables of one server: counts plus tile and slot lists.
 struct BatchDev {
     const int32_t *counts;   // [0] live tiles, [1] live slots
@@ -319,7 +327,7 @@ struct BatchDev {
     const SlotDesc *desc;
     SlotState *state;
     SlotStatus *status;
-    int tile_grid, slot_grid;
+    int tile_grid, vec_grid, slot_grid;   // workgroups: products, vector passes, per-slot sums
     int remap;   // tile order of the tile launches (TileIter: 0 round-robin, 1 contiguous eighths per XCD)
     int nt;      // 1: non-temporal loads of the matrix stream
 };

@@ -505,7 +505,9 @@ spk_status spk_server_create(spk_ctx ctx, size_t hbm_budget_bytes, int32_t max_s
         if (const char *t = std::strstr(e, "nt=")) nt = std::atoi(t + 3);
     }
     srv->B = spk::BatchDev{srv->d_counts, srv->d_tiles, srv->d_slots, srv->d_desc, srv->d_state, srv->d_status,
-                           std::min(srv->num_cu * occ, spk::kMaxGrid), std::min(srv->num_cu * 4, max_slots),
+                           std::min(srv->num_cu * occ, spk::kMaxGrid),
+                           std::min(srv->num_cu * spk::kTickVecBlocks, spk::kMaxGrid),
+                           std::min(srv->num_cu * 4, max_slots),
                            remap, nt};
     srv->stats.budget_bytes = static_cast<int64_t>(hbm_budget_bytes);
     srv->stats.max_slots = max_slots;
