@@ -364,9 +364,10 @@ __global__ __launch_bounds__(kBlock) void k_spmv_vector(int64_t n, const P *__re
 // reads and 64-bit address arithmetic per lane.  That row work, not the
 // stream, is what the coded tiles wait for (stencil7 N = 215 FP64: tiles
 // streamed into LDS alone 97 us, with the row sums 150).  us per product, codes
-// / patterns: stencil7 N = 215 FP64 in the CG loop 153 / 147.5, FP32 plain 82 /
-// 71; N = 512 FP32 in the loop 1,264 / 1,082.  Rows sum in storage order:
-// products equal the coded ones bit for bit.
+// / patterns: stencil7 N = 215 FP64 in the CG loop 153 / 147.5 (134 since the
+// loop leaves it its vectors in the Infinity Cache), FP32 plain 82 / 71; N =
+// 512 FP32 in the loop 1,264 / 1,082.  Rows sum in storage order: products
+// equal the coded ones bit for bit.
 struct PatMeta {
     TileMeta<RowPack> rows;
     uint8_t id;
