@@ -1741,7 +1741,7 @@ static spk_status run_resident(spk_plan pl, const double *b, double *x, spk::Per
         *done = result->epoch == a.epoch;
     } else {
         if ((s = pull(ctx, pl->h_st, pl->st, sizeof(SolveState))) != SPK_OK) return s;
-        *done = pl->h_st->base == static_cast<int64_t>(a.epoch);
+        *done = pl->h_st->launch == static_cast<int64_t>(a.epoch);
     }
     if (*done) return SPK_OK;
     if ((s = pull(ctx, ctl, pl->res_ctl, sizeof(ctl))) != SPK_OK) return s;

@@ -51,6 +51,7 @@ struct SolveState {
     void *x;              // solution vector of this solve (FP64 x, or FP32 d of an inner solve)
     double *hist;         // optional ||r_k|| history
     int64_t hist_cap;
+    int64_t launch;       // resident solves: the launch that wrote this state (nothing else writes it)
 };
 
 // Vector pairs of the fused CG loop: step k reads buffer (k + 1) & 1 of each
@@ -93,7 +94,7 @@ struct ResidentSolve {
     unsigned *ctl;            // kResidentCtl words, zero before the first launch
     unsigned epoch;           // 1, 2, ... per launch on these control words
     unsigned long long gate_ticks, spin_ticks;   // wall-clock limits of the start and of one wait
-    SolveState *st;           // FP64 solve: the state the host reads (base = epoch once done)
+    SolveState *st;           // FP64 solve: the state the host reads (launch = epoch once done)
     PersistResult *res;       // mixed solve: the result
     double tau, tau_in;
     int64_t max_iters, max_outer;

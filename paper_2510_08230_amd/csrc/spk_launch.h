@@ -200,7 +200,7 @@ size_t resident_lds_bytes(int64_t entries, bool mixed);
 size_t resident_exchange_bytes(int64_t n, bool mixed);
 // outer: the refinement's matrix of a mixed solve (same index arrays as A,
 // whose values are the inner solve's), nullptr for an FP64 solve on A.  The
-// launch leaves without a result (a.st->base / a.res->epoch is not a.epoch)
+// launch leaves without a result (a.st->launch / a.res->epoch is not a.epoch)
 // when its workgroups could not all start, or sets a.ctl[3] when a wait timed
 // out.
 hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, int grid, hipStream_t s);

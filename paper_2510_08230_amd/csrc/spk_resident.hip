@@ -490,7 +490,7 @@ __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
             S->iter = done;
             S->stop = stop;
             if (__hip_atomic_load(a.ctl + CTL_ERROR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-                S->base = static_cast<int64_t>(a.epoch);   // tells the host that the launch went through
+                S->launch = static_cast<int64_t>(a.epoch);   // tells the host that the launch went through
         }
     } else {
         int64_t inner = 0, outer = 0;
