@@ -783,9 +783,11 @@ constexpr size_t kResidentCtlBytes = 64 + sizeof(unsigned long long) * spk::kRes
 
 // Sets the plan's resident launch shape; false when a row is too long for one
 // thread or the workgroups' entries past the registers do not fit LDS.
-bool resident_shape(spk_plan pl, int rows, int64_t max_chunk, bool mixed) {
-    if (pl->A.max_row > spk::kResidentRowMax) return false;
-    const int64_t lds = pl->A.max_row <= spk::kResidentRegs ? 0 : max_chunk;
+// longest, max_chunk: as the validation found them (A.max_row may be 0 for
+// unknown).
+bool resident_shape(spk_plan pl, int rows, int64_t longest, int64_t max_chunk, bool mixed) {
+    if (longest > spk::kResidentRowMax) return false;
+    const int64_t lds = longest <= spk::kResidentRegs ? 0 : max_chunk;
     if (lds > INT32_MAX || spk::resident_lds_bytes(lds, mixed) > spk::kResidentLds) return false;
     pl->res_rows = rows;
     pl->res_lds = static_cast<int>(lds);
@@ -1175,6 +1177,13 @@ spk_status spk_partition(spk_ctx ctx, const spk_csr *A, int64_t parts, int64_t *
     return SPK_OK;
 }
 
+// CsrDev::max_row of a matrix whose longest row has max_row entries.
+// SPK_LONG_ROWS=0: every row summed by one lane, however long (comparisons).
+static int64_t known_max_row(int64_t max_row) {
+    const char *lr = std::getenv("SPK_LONG_ROWS");
+    return lr && std::strcmp(lr, "0") == 0 ? 0 : max_row;
+}
+
 static spk_status plan_common(spk_ctx ctx, const spk_csr *A, spk_plan *out, int64_t *max_row, int64_t chunk = 0,
                               int64_t *max_chunk = nullptr) {
     if (!ctx || !out) return SPK_ERR_INVALID_ARG;
@@ -1185,9 +1194,6 @@ static spk_status plan_common(spk_ctx ctx, const spk_csr *A, spk_plan *out, int6
     int32_t verdict = 0;
     s = gpu_verdict(ctx, A, &verdict, max_row, chunk, max_chunk);
     if (s != SPK_OK) return s;
-    // SPK_LONG_ROWS=0: every row summed by one lane, however long (comparisons)
-    const char *lr = std::getenv("SPK_LONG_ROWS");
-    if (max_row && lr && std::strcmp(lr, "0") == 0) *max_row = 0;
     if (verdict != SPK_CSR_OK) return fail(ctx, SPK_ERR_INVALID_ARG, std::string("malformed CSR: ") + verdict_name(verdict));
     return SPK_OK;
 }
@@ -1203,7 +1209,7 @@ spk_status spk_plan_spmv(spk_ctx ctx, const spk_csr *A, spk_plan *out) {
     pl->ctx = ctx;
     pl->kind = 0;
     pl->A = to_dev(A);
-    pl->A.max_row = max_row;
+    pl->A.max_row = known_max_row(max_row);
     return finish_spmv_plan(ctx, pl, A, out);
 }
 
@@ -1292,8 +1298,7 @@ spk_status spk_plan_spmv_coo(spk_ctx ctx, const spk_coo *A, spk_plan *out) {
         delete pl;
         return fail(ctx, SPK_ERR_DEVICE, "COO row lengths");
     }
-    const char *lr = std::getenv("SPK_LONG_ROWS");
-    pl->A.max_row = lr && std::strcmp(lr, "0") == 0 ? 0 : words[1];
+    pl->A.max_row = known_max_row(words[1]);
     return finish_spmv_plan(ctx, pl, &csr, out);
 }
 
@@ -1375,7 +1380,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
     pl->ctx = ctx;
     pl->kind = 1;
     pl->A = to_dev(A);
-    pl->A.max_row = max_row;
+    pl->A.max_row = known_max_row(max_row);
     pl->cfg = cfg;
     pl->algo = cfg.solver == SPK_SOLVER_CGS     ? ALGO_CGS
                : cfg.solver == SPK_SOLVER_GMRES ? ALGO_GMRES
@@ -1533,7 +1538,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         pl->tune32 = pl->tune;
         pl->tune = pl->A.split.xg ? make_tune(ctx, pl->A, 0, 0, 64, 1, 1, 0, 0, 0, 1) : heuristic_tune(ctx, pl->A);
     }
-    if (resident && resident_shape(pl, res_rows, max_chunk, mixed)) {
+    if (resident && resident_shape(pl, res_rows, max_row, max_chunk, mixed)) {
         const size_t cb = kResidentCtlBytes;
         if (!dget(cb, &pl->res_ctl) || !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch) ||
             (mixed && !dget(sizeof(spk::PersistResult), &pl->persist_res)))
@@ -2068,7 +2073,7 @@ spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg
     // the scratch keeps the last call's contents: clear the state and p by kernel
     SPK_HIP(ctx, spk::launch_fill_zero(pl.st, na_align(sizeof(SolveState)), ctx->num_cu, ctx->stream));
     SPK_HIP(ctx, spk::launch_fill_zero(pl.p, vb, ctx->num_cu * 4, ctx->stream));
-    if (resident && resident_shape(&pl, res_rows, max_chunk, false)) {
+    if (resident && resident_shape(&pl, res_rows, max_row, max_chunk, false)) {
         // slots in the partials, exchange buffers in r, p and q: the solve
         // uses neither when it runs as one launch, and when that launch
         // leaves without a result the loop initialises both

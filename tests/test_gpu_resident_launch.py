@@ -6,6 +6,7 @@ import torch
 
 import inputs
 from tests.gpu_util import DEV, dev_csr, to_dev
+from tests.test_gpu_resident import band
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +94,21 @@ def test_profiled_solves_do_not_pass_for_a_launch(spk, ctx, monkeypatch):
     spk.spk_free(loop)
     spk.spk_free(pl)
     assert all(good), good
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed_fp32"])
+@pytest.mark.parametrize("half", [3, 4, 5, 15, 16])
+def test_without_the_long_row_pass(spk, ctx, monkeypatch, precision, half):
+    """SPK_LONG_ROWS=0 leaves long rows to one lane; it does not change what a resident solve knows of its rows
+    (their entries past the registers' eight are kept in LDS), so solves are the same bit for bit."""
+    A = band(300, half, 4)
+    M = dev_csr(spk, A)
+    b = to_dev(inputs.rhs(A.n_rows, 4))
+    x0 = torch.zeros(A.n_rows, dtype=torch.float64, device=DEV)
+    out = []
+    for long_rows in ("1", "0"):
+        monkeypatch.setenv("SPK_LONG_ROWS", long_rows)
+        pl = plan(spk, ctx, monkeypatch, M, config(spk, precision), "1")
+        out.append(solve(spk, pl, b, x0))
+        spk.spk_free(pl)
+    assert out[0][1].stop_reason == spk.STOP_CONVERGED and same(out[1], out[0])
