@@ -102,7 +102,10 @@ typedef enum {
                                  (one row per thread of one 512-thread workgroup per CU, rows of at
                                  most 32 entries) as one launch that holds the matrix on the chip,
                                  or, when the device is too busy to run that launch's workgroups
-                                 together, and for every other solve, the host loop */
+                                 together, and for every other solve, the host loop.  A launch
+                                 whose workgroups wait for one another for 2 s is given up too:
+                                 the loop solves from the x passed in, and so does every later
+                                 solve of that plan */
     SPK_EXEC_HOST_LOOP = 1,   /* kernels launched from a host loop, status polled per chunk */
     SPK_EXEC_GRAPH = 2,       /* chunks of iterations replayed from a captured HIP graph */
     SPK_EXEC_PERSISTENT = 3   /* FP64 CG: the whole solve in one cooperative launch with grid

@@ -73,6 +73,7 @@ struct spk_ctx_s {
     void *scratch = nullptr;
     hipError_t scratch_err = hipSuccess;
     SolveState *h_noalloc_st = nullptr;
+    spk::ResidentState *h_noalloc_res = nullptr;
 };
 
 struct spk_plan_s {
@@ -89,8 +90,9 @@ struct spk_plan_s {
     spk_plan_info info{};
     // resident solve (one launch, the matrix on the chip; res_grid = 0: not used)
     int res_grid = 0, res_rows = 0, res_lds = 0;
-    unsigned res_epoch = 0;              // launches made on res_ctl
-    unsigned *res_ctl = nullptr;         // control words, then the grid-sum slots
+    unsigned res_epoch = 0;              // launches made on res_block
+    void *res_block = nullptr;           // kResidentBlockBytes
+    spk::ResidentState *h_res = nullptr; // its state, read back (pinned)
     void *res_xch = nullptr;             // exchange buffers
     double *r = nullptr, *p = nullptr, *q = nullptr, *partials = nullptr, *hist = nullptr;
     int algo = 0;                        // ALGO_CG / ALGO_CGS / ALGO_PCG
@@ -778,9 +780,6 @@ bool resident_wanted(spk_ctx ctx, const spk_solver_cfg &cfg, int64_t n) {
     return grid >= 1 && grid <= std::min(ctx->num_cu, spk::kResidentGrid) && cfg.max_iters <= kResidentMaxIters;
 }
 
-// Control words and grid-sum slots of a resident solve, in bytes.
-constexpr size_t kResidentCtlBytes = 64 + sizeof(unsigned long long) * spk::kResidentSlots;
-
 // Sets the plan's resident launch shape; false when a row is too long for one
 // thread or the workgroups' entries past the registers do not fit LDS.
 // longest, max_chunk: as the validation found them (A.max_row may be 0 for
@@ -1010,10 +1009,12 @@ void release_workspace(spk_plan pl) {
     ctx->dpool.put(pl->bar);
     ctx->dpool.put(pl->persist_res);
     pl->persist_res = nullptr;
-    ctx->dpool.put(pl->res_ctl);
+    ctx->dpool.put(pl->res_block);
     ctx->dpool.put(pl->res_xch);
-    pl->res_ctl = nullptr;
+    ctx->hpool.put(pl->h_res);
+    pl->res_block = nullptr;
     pl->res_xch = nullptr;
+    pl->h_res = nullptr;
     ctx->dpool.put(pl->rt);
     ctx->dpool.put(pl->u);
     ctx->dpool.put(pl->v);
@@ -1126,6 +1127,8 @@ spk_status spk_init(int device_id, void *hip_stream, spk_ctx *out) {
         hipMalloc(&ctx->d_probe, sizeof(long long) * spk::kCodeSlots + 4 * sizeof(unsigned)) != hipSuccess ||
         hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->ev_snap, hipEventDisableTiming) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->h_noalloc_res), sizeof(spk::ResidentState),
+                      hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&ctx->h_noalloc_st), sizeof(SolveState), hipHostMallocDefault) !=
             hipSuccess) {
         spk_finalize(ctx);
@@ -1150,6 +1153,7 @@ spk_status spk_finalize(spk_ctx ctx) {
     if (ctx->h_flags) (void)hipHostFree(ctx->h_flags);
     if (ctx->d_probe) (void)hipFree(ctx->d_probe);
     if (ctx->h_noalloc_st) (void)hipHostFree(ctx->h_noalloc_st);
+    if (ctx->h_noalloc_res) (void)hipHostFree(ctx->h_noalloc_res);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     if (ctx->ev_snap) (void)hipEventDestroy(ctx->ev_snap);
@@ -1539,13 +1543,11 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         pl->tune = pl->A.split.xg ? make_tune(ctx, pl->A, 0, 0, 64, 1, 1, 0, 0, 0, 1) : heuristic_tune(ctx, pl->A);
     }
     if (resident && resident_shape(pl, res_rows, max_row, max_chunk, mixed)) {
-        const size_t cb = kResidentCtlBytes;
-        if (!dget(cb, &pl->res_ctl) || !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch) ||
-            (mixed && !dget(sizeof(spk::PersistResult), &pl->persist_res)))
+        if (!dget(spk::kResidentBlockBytes, &pl->res_block) || !hget(sizeof(spk::ResidentState), &pl->h_res) ||
+            !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch))
             pl->res_grid = 0;   // no memory for it: the loop
-        else if (hipMemsetAsync(pl->res_ctl, 0, cb, ctx->stream) != hipSuccess ||
-                 hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess ||
-                 (mixed && hipMemsetAsync(pl->persist_res, 0, sizeof(spk::PersistResult), ctx->stream) != hipSuccess))
+        else if (hipMemsetAsync(pl->res_block, 0, spk::kResidentBlockBytes, ctx->stream) != hipSuccess ||
+                 hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess)
             return cleanup(SPK_ERR_DEVICE, "resident solve workspace");
     }
     int mode = cfg.exec_mode;
@@ -1709,10 +1711,12 @@ static spk_status run_persistent(spk_plan pl, const double *b, double *x) {
     return SPK_OK;
 }
 
-// One launch for the whole solve, its matrix on the chip.  *done = false: its
-// workgroups could not all start at once (the device is shared), nothing was
-// written, and the caller runs the launch-per-iteration loop instead.
-static spk_status run_resident(spk_plan pl, const double *b, double *x, spk::PersistResult *result, bool *done) {
+// One launch for the whole solve, its matrix on the chip.  *done = false: the
+// caller runs the launch-per-iteration loop instead, from the x it was given:
+// the launch's workgroups could not all start at once (the device is shared),
+// or one of its waits timed out.  After a time-out the plan stays with the
+// loop (each one costs seconds, and leaves the control words mid-solve).
+static spk_status run_resident(spk_plan pl, const double *b, double *x, bool *done) {
     spk_ctx ctx = pl->ctx;
     const spk_solver_cfg &cfg = pl->cfg;
     const bool mixed = cfg.precision != SPK_PREC_FP64;
@@ -1722,15 +1726,12 @@ static spk_status run_resident(spk_plan pl, const double *b, double *x, spk::Per
     a.b = b;
     a.x = x;
     a.xch = pl->res_xch;
-    a.ctl = pl->res_ctl;
-    a.slots = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(pl->res_ctl) + 64);
-    a.epoch = ++pl->res_epoch;
-    // 0.2 ms to start; SPK_RESIDENT=refuse: every launch leaves (tests)
-    const char *refuse = std::getenv("SPK_RESIDENT");
-    a.gate_ticks = refuse && std::strcmp(refuse, "refuse") == 0 ? 0 : static_cast<unsigned long long>(ctx->wall_khz) / 5;
+    a.epoch = pl->res_epoch + 1;
+    // 0.2 ms to start; SPK_RESIDENT=refuse: every launch leaves, =timeout: it
+    // runs, marked beforehand as one whose wait timed out (tests)
+    const char *env = std::getenv("SPK_RESIDENT");
+    a.gate_ticks = env && std::strcmp(env, "refuse") == 0 ? 0 : static_cast<unsigned long long>(ctx->wall_khz) / 5;
     a.spin_ticks = static_cast<unsigned long long>(ctx->wall_khz) * 2000ull;   // 2 s
-    a.st = pl->st;
-    a.res = pl->persist_res;
     a.tau = cfg.reduction_factor;
     a.tau_in = cfg.inner_reduction;
     a.max_iters = cfg.max_iters;
@@ -1738,19 +1739,24 @@ static spk_status run_resident(spk_plan pl, const double *b, double *x, spk::Per
     a.hist = pl->hist;
     a.hist_cap = pl->hist_cap;
     a.true_residual = cfg.true_residual;
-    SPK_HIP(ctx, spk::launch_resident(mixed ? pl->A32 : pl->A, mixed ? &pl->A : nullptr, a, pl->res_grid, ctx->stream));
-    unsigned ctl[spk::kResidentCtl] = {};
-    spk_status s = SPK_OK;
-    if (mixed) {
-        if ((s = pull(ctx, result, pl->persist_res, sizeof(*result))) != SPK_OK) return s;
-        *done = result->epoch == a.epoch;
-    } else {
-        if ((s = pull(ctx, pl->h_st, pl->st, sizeof(SolveState))) != SPK_OK) return s;
-        *done = pl->h_st->launch == static_cast<int64_t>(a.epoch);
+    const uint32_t mark = 1;
+    if (env && std::strcmp(env, "timeout") == 0)
+        SPK_HIP(ctx, hipMemcpyAsync(&static_cast<spk::ResidentState *>(pl->res_block)->failed, &mark, sizeof(mark),
+                                    hipMemcpyHostToDevice, ctx->stream));
+    SPK_HIP(ctx, spk::launch_resident(mixed ? pl->A32 : pl->A, mixed ? &pl->A : nullptr, a, pl->res_block, pl->res_grid,
+                                      ctx->stream));
+    pl->res_epoch = a.epoch;   // a launch that failed has left the control words as they were
+    spk_status s = pull(ctx, pl->h_res, pl->res_block, sizeof(spk::ResidentState));
+    if (s != SPK_OK) return s;
+    const bool failed = pl->h_res->failed != 0;   // never cleared: the plan's last launch
+    *done = pl->h_res->launch == a.epoch && !failed;
+    if (*done && !mixed) *pl->h_st = pl->h_res->st;
+    if (failed) {
+        pl->res_grid = 0;
+        SPK_HIP(ctx, hipMemcpyAsync(x, spk::resident_x0(pl->res_xch, pl->A.n_rows, mixed),
+                                    sizeof(double) * static_cast<size_t>(pl->A.n_rows), hipMemcpyDeviceToDevice,
+                                    ctx->stream));
     }
-    if (*done) return SPK_OK;
-    if ((s = pull(ctx, ctl, pl->res_ctl, sizeof(ctl))) != SPK_OK) return s;
-    if (ctl[3] != 0) return fail(ctx, SPK_ERR_DEVICE, "resident solve: a wait timed out");
     return SPK_OK;
 }
 
@@ -1760,7 +1766,7 @@ static spk_status execute_fp64(spk_plan pl, const double *b, double *x, spk_log 
     const int64_t n = pl->A.n_rows;
     spk_status s = SPK_OK;
     bool done = false;
-    if (pl->res_grid > 0 && !pl->profiling && (s = run_resident(pl, b, x, nullptr, &done)) != SPK_OK) return s;
+    if (pl->res_grid > 0 && !pl->profiling && (s = run_resident(pl, b, x, &done)) != SPK_OK) return s;
     if (done) {
         // the state is read back
     } else if (pl->right_jacobi && pl->bad_diag) {
@@ -1852,8 +1858,9 @@ static spk_status execute_mixed(spk_plan pl, const double *b, double *x, spk_log
     spk::PersistResult r{};
     bool whole = false;
     if (pl->res_grid > 0 && !pl->profiling) {
-        spk_status s = run_resident(pl, b, x, &r, &whole);
+        spk_status s = run_resident(pl, b, x, &whole);
         if (s != SPK_OK) return s;
+        if (whole) r = pl->h_res->res;
     }
     if (pl->persist_grid > 0) {
         spk_status s = run_persistent(pl, b, x);
@@ -2074,12 +2081,17 @@ spk_status spk_solve_noalloc(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg
     SPK_HIP(ctx, spk::launch_fill_zero(pl.st, na_align(sizeof(SolveState)), ctx->num_cu, ctx->stream));
     SPK_HIP(ctx, spk::launch_fill_zero(pl.p, vb, ctx->num_cu * 4, ctx->stream));
     if (resident && resident_shape(&pl, res_rows, max_row, max_chunk, false)) {
-        // slots in the partials, exchange buffers in r, p and q: the solve
-        // uses neither when it runs as one launch, and when that launch
-        // leaves without a result the loop initialises both
-        pl.res_ctl = reinterpret_cast<unsigned *>(pl.partials);
+        // the launch's block in the partials, exchange buffers from r on (6 vectors' worth
+        // at most, of at most 1 MB each): the solve uses neither when it runs
+        // as one launch, and when that launch leaves without a result the loop
+        // initialises both, after x has been put back from there
+        static_assert(kNaVecBase + 6 * na_align(sizeof(double) * spk::kResidentRows * spk::kResidentGrid) <=
+                      spk::kNoallocScratchBytes);
+        static_assert(spk::kResidentBlockBytes <= kNaPartialBytes);
+        pl.res_block = pl.partials;
+        pl.h_res = ctx->h_noalloc_res;
         pl.res_xch = pl.r;
-        SPK_HIP(ctx, spk::launch_fill_zero(pl.res_ctl, kResidentCtlBytes, ctx->num_cu, ctx->stream));
+        SPK_HIP(ctx, spk::launch_fill_zero(pl.res_block, spk::kResidentBlockBytes, ctx->num_cu, ctx->stream));
         SPK_HIP(ctx, spk::launch_fill_zero(pl.res_xch, (spk::resident_exchange_bytes(n, false) + 15) & ~size_t(15),
                                            ctx->num_cu * 4, ctx->stream));
     }

@@ -51,7 +51,6 @@ struct SolveState {
     void *x;              // solution vector of this solve (FP64 x, or FP32 d of an inner solve)
     double *hist;         // optional ||r_k|| history
     int64_t hist_cap;
-    int64_t launch;       // resident solves: the launch that wrote this state (nothing else writes it)
 };
 
 // Vector pairs of the fused CG loop: step k reads buffer (k + 1) & 1 of each
@@ -66,7 +65,6 @@ struct PersistResult {
     int64_t inner, outer;   // inner iterations in all, refinement steps
     double rnorm, bnorm;    // last ||b - A x|| (FP64) and ||b||
     int32_t stop;
-    uint32_t epoch;         // resident solves: the launch that wrote the result
 };
 
 // Resident solves (one launch per solve, the matrix held on the chip).
@@ -77,9 +75,26 @@ constexpr int kResidentRowMax = 32;     // longest row: one thread works through
 constexpr size_t kResidentLds = size_t(152) << 10;   // LDS for the rows' other entries (of 160 KB per CU)
 constexpr int kResidentTurns = 4;       // sets of exchange words used in turn
 constexpr int kResidentSlots = kResidentTurns * (8 + 16) * 4 * 16;   // words of the grid sums
-constexpr int kResidentCtl = 8;         // control words
+constexpr int kResidentCtl = 16;        // control words
 
-// Arguments of a resident solve (matrix fields and xd filled by the launcher).
+// What the host reads back after a resident launch.  A launch that leaves
+// early writes neither st, res nor launch.
+struct ResidentState {
+    SolveState st;             // FP64 solve
+    PersistResult res;         // mixed solve
+    uint32_t launch, failed;   // the launch that wrote the result; nonzero: a wait timed out
+};
+constexpr size_t kResidentStateBytes = 4096;
+static_assert(sizeof(ResidentState) <= kResidentStateBytes);
+// The device block of a plan's resident launches, zero before the first one:
+// the state, the control words, the words of the grid sums.  (Where the sums'
+// words lie is worth 1% of a solve: us for 36 steps with 256 B / 4 KB for the
+// state: stencil7 n = 97,336: 213.2 / 211.4, random n = 20,011: 264.7 / 262.9.)
+constexpr size_t kResidentBlockBytes =
+    kResidentStateBytes + sizeof(unsigned) * kResidentCtl + sizeof(unsigned long long) * kResidentSlots;
+
+// Arguments of a resident solve (the launcher fills in the matrix, xd, x0 and
+// the pointers into the plan's block).
 struct ResidentSolve {
     int64_t n;
     const void *rp, *ci, *va, *va64;
@@ -90,12 +105,12 @@ struct ResidentSolve {
     double *x;
     void *xch;                // exchange buffers (resident_exchange_bytes), zero before the first launch
     double *xd;
-    unsigned long long *slots;   // kResidentSlots words, zero before the first launch
-    unsigned *ctl;            // kResidentCtl words, zero before the first launch
-    unsigned epoch;           // 1, 2, ... per launch on these control words
+    double *x0;               // x as it was, for the loop that follows a time-out
+    ResidentState *state;     // the plan's block: the state, the control words, the words of the sums
+    unsigned *ctl;
+    unsigned long long *slots;
+    unsigned epoch;           // 1, 2, ... per launch on this block
     unsigned long long gate_ticks, spin_ticks;   // wall-clock limits of the start and of one wait
-    SolveState *st;           // FP64 solve: the state the host reads (launch = epoch once done)
-    PersistResult *res;       // mixed solve: the result
     double tau, tau_in;
     int64_t max_iters, max_outer;
     double *hist;

@@ -198,12 +198,14 @@ int persistent_blocks_per_cu(const CsrDev &A, const CsrDev *outer);
 // Resident solves: workgroup g holds rows [g * rows, (g + 1) * rows).
 size_t resident_lds_bytes(int64_t entries, bool mixed);
 size_t resident_exchange_bytes(int64_t n, bool mixed);
-// outer: the refinement's matrix of a mixed solve (same index arrays as A,
-// whose values are the inner solve's), nullptr for an FP64 solve on A.  The
-// launch leaves without a result (a.st->launch / a.res->epoch is not a.epoch)
-// when its workgroups could not all start, or sets a.ctl[3] when a wait timed
-// out.
-hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, int grid, hipStream_t s);
+const double *resident_x0(const void *xch, int64_t n, bool mixed);
+// block: kResidentBlockBytes of device memory, a ResidentState first.  outer:
+// the refinement's matrix of a mixed solve (same index arrays as A, whose
+// values are the inner solve's), nullptr for an FP64 solve on A.  The launch
+// leaves without a result (ResidentState::launch is not a.epoch) when its
+// workgroups could not all start; ResidentState::failed is set when a wait
+// timed out, and x may then be stored in part (resident_x0: x as it was).
+hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, void *block, int grid, hipStream_t s);
 
 // Workgroups of the SpMV kernel resident per CU for this tune/type (occupancy API).
 int spmv_blocks_per_cu(const CsrDev &A, const SpmvTune &t);

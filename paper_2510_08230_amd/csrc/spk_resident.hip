@@ -42,8 +42,11 @@
 // rendezvous.  If not every workgroup has started within a short time (the
 // device is shared with other streams' or processes' kernels), all of them
 // leave and the caller runs the launch-per-iteration loop instead; once all
-// have started, all stay until the solve ends.  Every wait is bounded by the
-// wall clock.
+// have started, all stay until the solve ends.  Every wait is bounded, by the
+// wall clock or by a count of polls: a workgroup whose wait ran out says so
+// (failed) and leaves, so the others finish, or run out of their waits and
+// leave too.  The caller then puts x back (x0) and runs the loop, whatever
+// they stored.
 #include "spk_fcg.h"
 #include "spk_launch.h"
 
@@ -109,7 +112,7 @@ __device__ __forceinline__ double row_total(double v) {
 }
 
 // Control words of a plan's resident launches.
-enum : int { CTL_ARRIVED = 0, CTL_GATE = 1, CTL_SYNCS = 2, CTL_ERROR = 3, CTL_PUBS = 4 };
+enum : int { CTL_ARRIVED = 0, CTL_GATE = 1, CTL_SYNCS = 2, CTL_PUBS = 4 };
 
 // 0 marks a word that its writer has not reached yet: a value of +0 goes out as -0.
 template <typename T>
@@ -130,6 +133,7 @@ __device__ __forceinline__ bool empty(T v) {
 // takes 256 x 256 x 4 words per poll; the same few cache lines then serve all
 // of them, which took 4.5 us at 254 workgroups against 0.8 us at 4.)
 constexpr int kGroup = 16;
+constexpr size_t kSlotsAt = kResidentStateBytes + sizeof(unsigned) * kResidentCtl;   // in the plan's block
 constexpr int kCopies = 8;
 
 struct GridSum {
@@ -137,9 +141,15 @@ struct GridSum {
     // copies, each polled by an eighth of the workgroups), then each group's
     // members' sums
     unsigned long long *slots;
-    unsigned *ctl;
     unsigned syncs;              // sums taken so far, over all launches of the plan
     unsigned long long ticks;
+    int *late;                   // LDS: a thread's words did not come
+
+    // (The word found from slots: a pointer to it costs registers in every step.)
+    __device__ __forceinline__ void fail() const {
+        ResidentState *state = reinterpret_cast<ResidentState *>(reinterpret_cast<char *>(slots) - kSlotsAt);
+        __hip_atomic_store(&state->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 
     __device__ __forceinline__ unsigned long long *set(unsigned turn, int which) const {
         return slots + (static_cast<size_t>(turn % kTurns) * (kCopies + kGroup) + which) * 4 * kGroup;
@@ -168,7 +178,7 @@ struct GridSum {
             w = get(word);
             want = empty(w);
             if ((spins & 63u) == 0 && wall_clock64() - t0 > ticks) {
-                __hip_atomic_store(ctl + CTL_ERROR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                fail();
                 bad = 1;
                 break;
             }
@@ -190,6 +200,7 @@ struct GridSum {
         const int G = gridDim.x, tid = threadIdx.x, lane = tid & 63;
         const int g = blockIdx.x, group = g / kGroup, member = g % kGroup, groups = (G + kGroup - 1) / kGroup;
         const int rows = blockDim.x >> 4, j = lane / kGroup, i = lane % kGroup;
+        const int gone = *late;   // read here, ahead of the barrier: its latency is hidden
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
             const double t = row_total(v[u]);
@@ -211,7 +222,7 @@ struct GridSum {
         }
         bool there = gather();   // the words of workgroups that are ahead are there already
         if (tid < 64) {
-            int bad = 0;
+            int bad = gone;
             const bool one = groups == 1;   // its members' slots are read directly
             if (member == 0 && !one) {
                 const double t = collect(set(syncs, kCopies + group), lane, j < NV && group * kGroup + i < G, bad);
@@ -227,7 +238,8 @@ struct GridSum {
         for (unsigned spins = 0; !there; ++spins) {
             there = gather();
             if (spins > kMaxSpins) {
-                __hip_atomic_store(ctl + CTL_ERROR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                fail();
+                *late = 1;   // the workgroup leaves at one of the next sums
                 break;
             }
         }
@@ -269,8 +281,10 @@ __device__ __forceinline__ bool rendezvous(unsigned *ctl, unsigned epoch, unsign
 template <typename T, typename V, typename V64>
 __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
     extern __shared__ char smem[];
+    __shared__ int s_late;
+    if (threadIdx.x == 0) s_late = 0;
     if (!rendezvous(a.ctl, a.epoch, a.gate_ticks)) return;
-    GridSum grid{a.slots, a.ctl, a.ctl[CTL_SYNCS], a.spin_ticks};
+    GridSum grid{a.slots, a.ctl[CTL_SYNCS], a.spin_ticks, &s_late};
     unsigned pubs = a.ctl[CTL_PUBS];   // vectors exchanged so far, over all launches of the plan
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * a.rows;
@@ -434,6 +448,7 @@ __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
 
     const double bi = has ? a.b[row] : 0.0;
     double xi = has ? a.x[row] : 0.0;
+    if (has) a.x0[row] = xi;
     auto caller_x = [&](unsigned off) { return *at(a.x, off); };
     auto shared_x = [&](unsigned off) { return get(at(a.xd, off)); };
     if constexpr (std::is_same_v<T, double>) {
@@ -451,7 +466,7 @@ __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
         } else if (!isfinite(rho)) stop = STOP_NON_FINITE;
         else if (res <= a.tau * bn) stop = STOP_CONVERGED;
         else if (a.max_iters <= 0) stop = STOP_MAX_ITERS;
-        SolveState *S = a.st;
+        SolveState *S = &a.state->st;
         if (lead) {
             S->x = a.x;
             S->hist = a.hist;
@@ -489,8 +504,6 @@ __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
         if (lead) {
             S->iter = done;
             S->stop = stop;
-            if (__hip_atomic_load(a.ctl + CTL_ERROR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-                S->launch = static_cast<int64_t>(a.epoch);   // tells the host that the launch went through
         }
     } else {
         int64_t inner = 0, outer = 0;
@@ -546,15 +559,15 @@ __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
         }
         if (has && (outer > 0 || bn == 0.0)) a.x[row] = xi;
         if (lead) {
-            a.res->inner = inner;
-            a.res->outer = outer;
-            a.res->rnorm = rnorm;
-            a.res->bnorm = bn;
-            a.res->stop = stop;
-            if (__hip_atomic_load(a.ctl + CTL_ERROR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) a.res->epoch = a.epoch;
+            a.state->res.inner = inner;
+            a.state->res.outer = outer;
+            a.state->res.rnorm = rnorm;
+            a.state->res.bnorm = bn;
+            a.state->res.stop = stop;
         }
     }
     if (lead) {
+        a.state->launch = a.epoch;   // tells the host that the launch went through
         a.ctl[CTL_SYNCS] = grid.syncs;
         a.ctl[CTL_PUBS] = pubs;
     }
@@ -579,12 +592,21 @@ size_t resident_lds_bytes(int64_t entries, bool mixed) {
     return static_cast<size_t>(entries) * (4 * t + sizeof(int));
 }
 
-size_t resident_exchange_bytes(int64_t n, bool mixed) {
+// The exchange buffers: kTurns vectors of the iterations' type, then xd and x0.
+static size_t resident_xd_at(int64_t n, bool mixed) {
     const size_t t = mixed ? sizeof(float) : sizeof(double);
-    return ((kTurns * t * static_cast<size_t>(n) + 255) & ~size_t(255)) + sizeof(double) * static_cast<size_t>(n);
+    return (kTurns * t * static_cast<size_t>(n) + 255) & ~size_t(255);
 }
 
-hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, int grid, hipStream_t s) {
+size_t resident_exchange_bytes(int64_t n, bool mixed) {
+    return resident_xd_at(n, mixed) + 2 * sizeof(double) * static_cast<size_t>(n);
+}
+
+const double *resident_x0(const void *xch, int64_t n, bool mixed) {
+    return reinterpret_cast<const double *>(static_cast<const char *>(xch) + resident_xd_at(n, mixed)) + n;
+}
+
+hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a, void *block, int grid, hipStream_t s) {
     const bool mixed = outer != nullptr;
     if (a.rows < 1 || a.rows > kResidentRows || grid < 1 || grid > kResidentGrid || static_cast<int64_t>(grid) * a.rows < A.n_rows ||
         A.n_rows > INT32_MAX)
@@ -596,9 +618,11 @@ hipError_t launch_resident(const CsrDev &A, const CsrDev *outer, ResidentSolve a
     a.ptr_t = A.ptr_t;
     a.idx_t = A.idx_t;
     a.va64 = outer ? outer->va : A.va;
-    const size_t t = mixed ? sizeof(float) : sizeof(double);
-    a.xd = reinterpret_cast<double *>(static_cast<char *>(a.xch) +
-                                      ((kTurns * t * static_cast<size_t>(a.n) + 255) & ~size_t(255)));
+    a.xd = reinterpret_cast<double *>(static_cast<char *>(a.xch) + resident_xd_at(a.n, mixed));
+    a.x0 = a.xd + a.n;
+    a.ctl = reinterpret_cast<unsigned *>(static_cast<char *>(block) + kResidentStateBytes);
+    a.slots = reinterpret_cast<unsigned long long *>(static_cast<char *>(block) + kSlotsAt);
+    a.state = static_cast<ResidentState *>(block);
     const int threads = (a.rows + 63) & ~63;   // one per row
     const void *k = kernel_for(A, outer);
     if (threads > kResidentRows || !k) return hipErrorInvalidValue;

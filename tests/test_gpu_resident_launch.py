@@ -1,6 +1,8 @@
 """How a plan's resident launch (one launch per small CG solve) is told from
-the loop that takes its place: every solve of a plan whose launches are refused
-equals the loop's, whatever its number, caps and chunk length."""
+the loop that takes its place: every solve of a plan whose launches are refused, or
+whose waits time out, equals the loop's, whatever its number, caps and chunk
+length.  (A time-out is a mark set from the host: the launch itself runs as
+usual and stores x, which has to be put back.)"""
 import pytest
 import torch
 
@@ -112,3 +114,35 @@ def test_without_the_long_row_pass(spk, ctx, monkeypatch, precision, half):
         out.append(solve(spk, pl, b, x0))
         spk.spk_free(pl)
     assert out[0][1].stop_reason == spk.STOP_CONVERGED and same(out[1], out[0])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed_fp32"])
+@pytest.mark.parametrize("kind,size", [("stencil7", 8), ("band", 4097)])
+def test_after_a_timeout_the_plan_stays_with_the_loop(spk, ctx, monkeypatch, precision, kind, size):
+    A = inputs.stencil7(size, 1) if kind == "stencil7" else band(size, 4, 1)
+    M = dev_csr(spk, A)
+    loop = plan(spk, ctx, monkeypatch, M, config(spk, precision), "0")
+    pl = plan(spk, ctx, monkeypatch, M, config(spk, precision), "1")
+    x0 = to_dev(inputs.vec(A.n_rows, 1, 9))
+    good = []
+    for k, mode in enumerate(("refuse", "timeout", "1", "refuse", "1")):
+        b = to_dev(inputs.vec(A.n_rows, 3, k))
+        monkeypatch.setenv("SPK_RESIDENT", mode)
+        got = solve(spk, pl, b, x0)
+        want = solve(spk, loop, b, x0)
+        good.append(got[1].stop_reason == spk.STOP_CONVERGED and same(got, want))
+    spk.spk_free(loop)
+    spk.spk_free(pl)
+    assert all(good), good
+
+
+def test_noalloc_solve_after_a_timeout(spk, ctx, monkeypatch):
+    A = band(4097, 4, 1)
+    M = dev_csr(spk, A)
+    b, x0 = to_dev(inputs.rhs(A.n_rows, 3)), to_dev(inputs.vec(A.n_rows, 1, 9))
+    out = []
+    for mode in ("0", "timeout", "refuse"):
+        monkeypatch.setenv("SPK_RESIDENT", mode)
+        x = x0.clone()
+        out.append((x, spk.spk_solve_noalloc(ctx, M, b, x, config(spk, "fp64"))))
+    assert same(out[1], out[0]) and same(out[2], out[0])
