@@ -274,6 +274,7 @@ int split_shift(const CsrDev &A, bool f64) {
     if (env && std::strcmp(env, "0") == 0) return -1;
     const bool forced = env && std::strcmp(env, "1") == 0;
     if (A.codes || !stream_ok(A) || A.n_rows < 1 || A.n_cols < 1 || A.nnz < 1 || A.nnz > INT32_MAX) return -1;
+    if (A.max_row > spk::kLongRow && !A.pieces) return -1;   // the split tiles take long rows from their pieces
     if (!forced && (A.nnz > 7.5 * A.n_rows || A.nnz < (int64_t(1) << 22))) return -1;
     for (int shift : {f64 ? spk::kSplitLocal - 1 : spk::kSplitLocal, 17, 18, 19})
         if (((A.n_cols - 1) >> shift) < spk::kSplitBlocks) return shift;

@@ -502,8 +502,8 @@ k_spmv_pattern(int64_t n, int64_t nnz, const RowPack *__restrict__ rp, const uin
 // of one block (some 3 of a tile's 1,792 entries at 611 blocks, 12 of a group
 // of four tiles') share lines: 1.9 GB fetched where 1.5 are needed, at 4.4
 // TB/s.  Groups of 2, 8 and 16 tiles measure the same.  Row sums run in
-// storage order on the caller's values, so products equal the plain ones bit
-// for bit.  Random pattern, 7 entries per row, us per call, plain / split (the
+// storage order on the caller's values, and rows longer than kLongRow from
+// their pieces, so products equal the plain ones bit for bit.  Random pattern, 7 entries per row, us per call, plain / split (the
 // two launches): FP64 n = 1e6 68 / 58 (17 + 32), n = 2e6 180 / 98, n = 1e7
 // 1,186 / 587 (145 + 430; with the slices of 128 blocks gathered from L2,
 // 795: 474 + 322); FP32 n = 3e6 228 / 102.
@@ -627,6 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
             const int64_t row = cur.r0 + threadIdx.x;
             const int64_t s = cur.first(), e = cur.end();
             const int64_t a = cur.lo(), b = cur.hi();
+            const bool lng = lra.base && row < r1 && b - a > kLongRow;   // its pieces have been summed
             if (e - s <= kStreamCap) {
                 dma_chunks<V>(va, s, e, nnz, lv, nt);
                 dma_chunks<uint16_t>(sp.perm, s, e, nnz, lp, nt);
@@ -655,7 +656,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
                 __builtin_amdgcn_s_waitcnt(0);   // this wave's DMA has landed
                 __syncthreads();                 // ... and every other wave's
                 __builtin_amdgcn_s_setprio(2);   // (as in spmv_tiles_lds)
-                if (row < r1)
+                if (row < r1 && !lng)
                     emit_row(epi, row,
                              row_from_lds<V, uint16_t, C>(reinterpret_cast<const V *>(lv),
                                                           reinterpret_cast<const uint16_t *>(lp), a, b,
@@ -668,14 +669,13 @@ __global__ __launch_bounds__(kBlock) void k_spmv_split(int64_t n, int64_t nnz, c
             } else {
                 if (more) nxt.load(rp, n, after.tile());
                 const PlainGather<X, C> gx{x};
-                if (row < r1 && lra.base && b - a > kLongRow)   // its pieces have been summed
-                    epi.row(row, lra.template sum<C>(row, b - a));
-                else if (row < r1)
+                if (row < r1 && !lng)
                     epi.row(row, ci64 ? row_from_global<V, int64_t, C, kRowUnroll>(va, static_cast<const int64_t *>(ci), a,
                                                                                    b, gx, nt)
                                       : row_from_global<V, int32_t, C, kRowUnroll>(va, static_cast<const int32_t *>(ci), a,
                                                                                    b, gx, nt));
             }
+            if (lng) epi.row(row, lra.template sum<C>(row, b - a));
             if (!more) break;
             it = after;
             cur = nxt;
