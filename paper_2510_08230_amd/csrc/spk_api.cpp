@@ -33,10 +33,12 @@ struct TuneKey {
     int codes;   // the matrix has column codes
     int staged;  // values and columns are 16-byte aligned (the LDS tiles may run)
     int long_rows;    // rows longer than kLongRow (the kernels with the long-row pass run)
-    int split;        // the plan may split the gathers (split_rule)
+    int split;        // the plan has split gathers (they are timed too)
+    int pats;         // ... row patterns
     bool operator<(const TuneKey &o) const {
-        return std::tie(n_rows, n_cols, nnz, pt, it, vt, use, codes, staged, long_rows, split) <
-               std::tie(o.n_rows, o.n_cols, o.nnz, o.pt, o.it, o.vt, o.use, o.codes, o.staged, o.long_rows, o.split);
+        return std::tie(n_rows, n_cols, nnz, pt, it, vt, use, codes, staged, long_rows, split, pats) <
+               std::tie(o.n_rows, o.n_cols, o.nnz, o.pt, o.it, o.vt, o.use, o.codes, o.staged, o.long_rows, o.split,
+                        o.pats);
     }
 };
 
@@ -283,7 +285,7 @@ int split_shift(const CsrDev &A, bool f64) {
 
 TuneKey tune_key(const CsrDev &A, int use) {
     return TuneKey{A.n_rows, A.n_cols, A.nnz, A.ptr_t, A.idx_t, A.val_t, use, A.codes != nullptr, stream_ok(A),
-                   A.max_row > spk::kLongRow, A.split.xg != nullptr || split_shift(A, true) >= 0};
+                   A.max_row > spk::kLongRow, A.split.xg != nullptr, A.patterns != nullptr};
 }
 
 // Times each candidate and keeps the fastest.  x, y: device vectors of the
@@ -362,6 +364,11 @@ spk_status autotune(spk_ctx ctx, const CsrDev &A, const void *x, void *y, int us
         if (per < 0.97 * best.ms) best = TuneResult{t, per};
     }
     if (A.split.xg) {
+        // what a plan without the split runs (none built, dropped as slower,
+        // or the allocation-free solve)
+        TuneKey plain = key;
+        plain.split = 0;
+        ctx->tune_cache.emplace(plain, best);
         // the gathers ahead in column order, on the XCD-blocked tile order
         // with streamed matrix loads (both launches are timed)
         const SpmvTune c = make_tune(ctx, A, 0, 0, 64, 1, 1, 0, 0, 0, 1);
@@ -581,7 +588,9 @@ spk_status build_split(spk_plan pl, int use, int vt) {
     if (forced && *forced && !std::strstr(forced, "split=1")) return SPK_OK;
     CsrDev probe = A;
     probe.val_t = vt;
-    const auto hit = ctx->tune_cache.find(tune_key(probe, use));
+    TuneKey key = tune_key(probe, use);
+    key.split = 1;
+    const auto hit = ctx->tune_cache.find(key);
     if (hit != ctx->tune_cache.end() && !hit->second.tune.split) return SPK_OK;
     const int blocks = static_cast<int>((A.n_cols - 1) >> shift) + 1;
     const size_t bytes = spk::split_buffer_bytes(A.n_rows, A.nnz, blocks, shift);
