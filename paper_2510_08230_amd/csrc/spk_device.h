@@ -161,6 +161,13 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The same among the lanes of one wave, whose other waves may be gone.
+__device__ __forceinline__ void lds_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Block-level fixed-order reduction of NV doubles; thread 0 stores the
 // workgroup's partials at partials[j * kMaxGrid + blockIdx.x].
 template <int NV>

@@ -552,6 +552,7 @@ __global__ __launch_bounds__(kMidThreads) void k_gm_final(SolveState *st, GmresS
         gs->Hu[tid * kMaxKrylov + j] = c;
         col[tid] = c;
     }
+    lds_wave_sync();   // lane 0 reads every lane's term
     if (tid != 0) return;
     gs->Hu[(j + 1) * kMaxKrylov + j] = hn;
     double *H = gs->H;
