@@ -771,6 +771,16 @@ __device__ __forceinline__ int code_lookup(const long long *key, const unsigned 
     return -1;
 }
 
+// Whether *word is set, the same in every thread of the workgroup: one thread
+// reads it, since other workgroups of the launch set it while this one starts
+// and two waves could see it differently ahead of the kernel's barriers.
+__device__ __forceinline__ bool given_up(const unsigned *word) {
+    __shared__ unsigned v;
+    if (threadIdx.x == 0) v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return v != 0;
+}
+
 template <typename P, typename I>
 __global__ __launch_bounds__(kBlock) void k_code_encode(int64_t n_rows, const P *__restrict__ rp,
                                                         const I *__restrict__ ci, const int64_t *__restrict__ dict,
@@ -779,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_code_encode(int64_t n_rows, const P 
     __shared__ unsigned char code[kCodeLdsSlots];
     __shared__ unsigned short row_of[kStreamCap];
     const unsigned nd = words[0];
-    if (words[1] != 0 || nd < 1 || nd > static_cast<unsigned>(kCodeDict)) return;   // no codes: uniform
+    if (given_up(words + 1) || nd < 1 || nd > static_cast<unsigned>(kCodeDict)) return;   // no codes: uniform
     const int ndict = static_cast<int>(nd);
     // offset -> code map: the ndict distinct table entries each claim a slot
     for (int i = threadIdx.x; i < kCodeLdsSlots; i += kBlock) key[i] = kCodeEmpty;
@@ -1002,7 +1012,7 @@ __global__ __launch_bounds__(kBlock) void k_pat_verify(int64_t n, const RowPack 
     __shared__ int64_t off[kCodeDict];
     __shared__ uint32_t info[kPatterns];
     __shared__ int32_t offs[kPatternOffs];
-    if (words[1] != 0) return;   // uniform
+    if (given_up(words + 1)) return;   // uniform
     for (int i = threadIdx.x; i < kCodeDict; i += kBlock) off[i] = dict[i];
     for (int i = threadIdx.x; i < kPatterns; i += kBlock) info[i] = tab->info[i];
     for (int i = threadIdx.x; i < kPatternOffs; i += kBlock) offs[i] = tab->offs[i];
