@@ -922,7 +922,7 @@ __device__ __forceinline__ int pat_slot(unsigned long long key, int64_t row, boo
         unsigned h = static_cast<unsigned>(pat_mix(k0) >> 56);
         int found = -1;
         for (int probe = 0; probe < kPatterns && found < 0; ++probe, h = (h + 1u) & (kPatterns - 1u)) {
-            unsigned long long k = seen[h];
+            unsigned long long k = __hip_atomic_load(seen + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (k == 0) {
                 k = __hip_atomic_load(keys + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (k == 0) {
@@ -934,7 +934,8 @@ __device__ __forceinline__ int pat_slot(unsigned long long key, int64_t row, boo
                     old = lane_word(old, leader);
                     k = old == 0 ? k0 : old;
                 }
-                seen[h] = k;    // whoever gets here stores the same key
+                // whoever gets here stores the same key, whole: other waves read it meanwhile
+                __hip_atomic_store(seen + h, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             if (k == k0) found = static_cast<int>(h);
         }

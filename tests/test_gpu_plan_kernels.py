@@ -64,3 +64,19 @@ def test_long_patterns_checked(spk, ctx, monkeypatch, length):
     same, c1 = product(spk, ctx, monkeypatch, A, "1", "stream,pats=1")
     # 64 offsets: the rows at the ends make 3,104 offsets in all, past the table's 1,024
     assert c1 == (3 if length == 64 else 7) and torch.equal(same, plain)
+
+
+def test_many_patterns_named_by_many_waves(spk, ctx, monkeypatch):
+    """256 distinct rows of 0 to 8 entries, every one of them in every workgroup: the waves share what they have
+    seen of the table while it fills."""
+    n, kinds = 300_001, 256
+    kind = (np.arange(n) * 97) % kinds
+    bits = (kind[:, None] >> np.arange(8)[None, :]) & 1
+    cols = (np.arange(n)[:, None] + np.arange(8)[None, :])[bits == 1].astype(np.int32)
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(bits.sum(1), out=rp[1:])
+    A = inputs.CSR(n, n + 8, rp, cols, np.random.default_rng(5).uniform(-1, 1, cols.size))
+    plain, _ = product(spk, ctx, monkeypatch, A, "1", "stream,pats=0")
+    for _ in range(3):
+        same, c1 = product(spk, ctx, monkeypatch, A, "1", "stream,pats=1")
+        assert c1 == 7 and torch.equal(same, plain)
