@@ -672,6 +672,27 @@ spk_status build_pieces(spk_plan pl) {
     return SPK_OK;
 }
 
+// Gives back what only makes the products faster (row patterns, split gathers,
+// long rows' pieces), before the tuner has chosen among them; false when there
+// is nothing.  Such a plan runs as one that had no memory to build them.
+bool shed_structures(spk_plan pl) {
+    if (!pl->pat_buf && !pl->split_buf && !pl->long_buf) return false;
+    (void)hipStreamSynchronize(pl->ctx->stream);
+    for (void **buf : {&pl->pat_buf, &pl->split_buf, &pl->long_buf}) {
+        pl->ctx->dpool.put(*buf);
+        *buf = nullptr;
+    }
+    for (CsrDev *A : {&pl->A, &pl->A32, &pl->A_orig}) {
+        A->patterns = nullptr;
+        A->split = spk::SplitDev{};
+        A->pieces = nullptr;
+        A->n_pieces = 0;
+        A->long_base = nullptr;
+        A->piece_sums = nullptr;
+    }
+    return true;
+}
+
 // ------------------------------------------------------------------ profiling events
 // idx (optional): the recorded launch's event index, -1 when not sampled.
 spk_status prof_begin(spk_plan pl, hipEvent_t *end_ev, int64_t *idx = nullptr) {
@@ -1409,12 +1430,14 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         delete pl;
         return fail(ctx, code, msg);
     };
-    auto dget = [&](size_t bytes, auto **out) {
+    auto dtry = [&](size_t bytes, auto **out) {
         void *v = nullptr;
         const bool ok = ctx->dpool.get(bytes, &v) == hipSuccess;
         *out = static_cast<std::remove_reference_t<decltype(*out)>>(v);
         return ok;
     };
+    // what the solve cannot do without, in place of what it can (until it is tuned)
+    auto dget = [&](size_t bytes, auto **out) { return dtry(bytes, out) || (shed_structures(pl) && dtry(bytes, out)); };
     auto hget = [&](size_t bytes, auto **out) {
         void *v = nullptr;
         const bool ok = ctx->hpool.get(bytes, &v) == hipSuccess;
@@ -1512,7 +1535,7 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
                                                                   : SPK_F32;
             const size_t width = to == SPK_F32 ? 4 : 2;
             void *dst = nullptr;
-            if (ctx->dpool.get(std::max<size_t>(1, A->nnz * width), &dst) != hipSuccess)
+            if (!dget(std::max<size_t>(1, A->nnz * width), &dst))
                 return cleanup(SPK_ERR_OUT_OF_MEMORY, "low-precision value copy");
             pl->a32_vals = dst;
             if (A->nnz > 0 && spk::launch_round_values(A->nnz, static_cast<const double *>(A->values), dst, to,
@@ -1553,8 +1576,8 @@ spk_status spk_plan_solve(spk_ctx ctx, const spk_csr *A, const spk_solver_cfg *c
         pl->tune = pl->A.split.xg ? make_tune(ctx, pl->A, 0, 0, 64, 1, 1, 0, 0, 0, 1) : heuristic_tune(ctx, pl->A);
     }
     if (resident && resident_shape(pl, res_rows, max_row, max_chunk, mixed)) {
-        if (!dget(spk::kResidentBlockBytes, &pl->res_block) || !hget(sizeof(spk::ResidentState), &pl->h_res) ||
-            !dget(spk::resident_exchange_bytes(n, mixed), &pl->res_xch))
+        if (!dtry(spk::kResidentBlockBytes, &pl->res_block) || !hget(sizeof(spk::ResidentState), &pl->h_res) ||
+            !dtry(spk::resident_exchange_bytes(n, mixed), &pl->res_xch))
             pl->res_grid = 0;   // no memory for it: the loop
         else if (hipMemsetAsync(pl->res_block, 0, spk::kResidentBlockBytes, ctx->stream) != hipSuccess ||
                  hipMemsetAsync(pl->res_xch, 0, spk::resident_exchange_bytes(n, mixed), ctx->stream) != hipSuccess)
