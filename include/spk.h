@@ -99,17 +99,21 @@ typedef enum {
 } spk_precond;
 typedef enum {
     SPK_EXEC_AUTO = 0,        /* the library's choice: CG without a preconditioner on a small system
-                                 (one row per thread of one 512-thread workgroup per CU, rows of at
-                                 most 32 entries) as one launch that holds the matrix on the chip,
-                                 or, when the device is too busy to run that launch's workgroups
+                                 (one row per thread of one 512-thread workgroup per CU; rows of at
+                                 most 32 entries and, where any row passes 8, at most 4,323 entries,
+                                 7,782 in mixed precision, per workgroup: 256 rows up to n = 32,768,
+                                 512 above; max_iters of at most 100,000) as one launch that holds
+                                 the matrix on the chip, or, when the device is too busy to run that launch's workgroups
                                  together, and for every other solve, the host loop.  A launch
                                  whose workgroups wait for one another for 2 s is given up too:
                                  the loop solves from the x passed in, and so does every later
                                  solve of that plan */
     SPK_EXEC_HOST_LOOP = 1,   /* kernels launched from a host loop, status polled per chunk */
     SPK_EXEC_GRAPH = 2,       /* chunks of iterations replayed from a captured HIP graph */
-    SPK_EXEC_PERSISTENT = 3   /* FP64 CG: the whole solve in one cooperative launch with grid
+    SPK_EXEC_PERSISTENT = 3,  /* FP64 CG: the whole solve in one cooperative launch with grid
                                  barriers (other solves fall back to SPK_EXEC_GRAPH) */
+    SPK_EXEC_RESIDENT = 4     /* reported by spk_plan_get_info only: AUTO chose the one launch that
+                                 holds the matrix on the chip */
 } spk_exec_mode;
 
 typedef struct spk_ctx_s *spk_ctx;
@@ -174,7 +178,8 @@ typedef struct {
     int32_t lanes;             /* lanes per row of the vector kernel */
     int32_t grid;              /* SpMV workgroups */
     int32_t xcd_remap;         /* tile order: 0 round-robin, 1 XCD eighths, k >= 2 XCD blocks of k tiles */
-    int32_t exec_mode;         /* resolved spk_exec_mode */
+    int32_t exec_mode;         /* resolved spk_exec_mode; RESIDENT turns to HOST_LOOP if a launch of
+                                  the plan was given up after a wait */
     int32_t chunk_iters;       /* resolved chunk size */
     int32_t tuned;             /* 1 = chosen by timing candidates, 0 = heuristic/cached */
     int32_t col_codes;         /* bit 0: the row-tile SpMV reads one byte per entry naming
@@ -184,9 +189,11 @@ typedef struct {
                                   256-row tile, a uint16 offset per row) in place of row_ptr;
                                   bit 2: with both, it reads one byte per row naming the row's
                                   whole sequence of offsets in a table of at most 256 distinct
-                                  rows, in place of the entries' bytes */
+                                  rows, in place of the entries' bytes;
+                                  bit 3 (8): the gathers of x run ahead in column order, in a
+                                  launch of their own, and no other bit is set */
     double spmv_ms;            /* measured time of the chosen SpMV (0 if not tuned) */
-    int32_t fused_loop;        /* 1 = CG runs one launch per iteration: the SpMV step also forms
+    int32_t fused_loop;        /* 1 = CG (its loop, where exec_mode is RESIDENT) runs one launch per iteration: the SpMV step also forms
                                   the direction from the previous r, q and p at every gathered
                                   column and updates x, r and p (0 = three launches) */
     int32_t nontemporal;       /* 1 = the row-tile SpMV streams the matrix with non-temporal loads */
@@ -283,7 +290,8 @@ spk_status spk_plan_get_info(spk_plan plan, spk_plan_info *info);
 /* Per-kernel timing: with on = k >= 1, every k-th launch of the plan's
  * dominant SpMV kernel (launches 0, k, 2k, ... of each solve, counting
  * only launches that did work) is bracketed by HIP events on the context
- * stream; on <= 0 turns timing off.  Stats return the summed device time
+ * stream; on <= 0 turns timing off.  While it is on, a plan whose exec_mode
+ * is RESIDENT runs the loop, whose launches can be timed.  Stats return the summed device time
  * (ms) and the count of timed launches since the last reset. */
 spk_status spk_plan_set_profiling(spk_plan plan, int32_t on);
 spk_status spk_plan_kernel_stats(spk_plan plan, double *total_ms, int64_t *launches);

@@ -483,7 +483,8 @@ spk_status choose_tune(spk_plan pl, const void *x, void *y, int use = TUNE_PLAIN
     pl->info.col_codes =
         (pl->tune.kind == 0 && pl->tune.codes && A.codes)
             ? ((pl->tune.pack && A.rowpack) ? ((pl->tune.pats && A.patterns) ? 7 : 3) : 1)
-            : 0;
+        : (pl->tune.kind == 0 && pl->tune.split && A.split.xg) ? 8
+                                                               : 0;
     return SPK_OK;
 }
 
@@ -2160,6 +2161,7 @@ spk_status spk_plan_history(spk_plan pl, double *out, int64_t cap, int64_t *coun
 spk_status spk_plan_get_info(spk_plan pl, spk_plan_info *info) {
     if (!pl || !info) return SPK_ERR_INVALID_ARG;
     *info = pl->info;
+    if (pl->res_grid > 0) info->exec_mode = SPK_EXEC_RESIDENT;
     return SPK_OK;
 }
 

@@ -31,6 +31,7 @@ SOLVER_CG, SOLVER_CGS, SOLVER_GMRES = 0, 1, 2
 PRECOND_NONE, PRECOND_JACOBI = 0, 1
 PREC_FP64, PREC_MIXED_FP32, PREC_MIXED_BF16, PREC_MIXED_FP16 = range(4)
 EXEC_AUTO, EXEC_HOST_LOOP, EXEC_GRAPH, EXEC_PERSISTENT = range(4)
+EXEC_RESIDENT = 4   # reported by spk_plan_get_info only
 
 
 class SpkError(RuntimeError):
