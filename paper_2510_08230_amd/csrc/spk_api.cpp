@@ -800,7 +800,7 @@ spk_status pattern_regular(spk_ctx ctx, const CsrDev &A, bool *regular) {
 int resident_rows(int64_t n) { return n <= 32768 ? 256 : spk::kResidentRows; }
 
 // Whether a solve of this configuration may run as one resident launch (its
-// entries still have to fit, resident_fits): CG in the library's own choice of
+// entries still have to fit, resident_shape): CG in the library's own choice of
 // execution, unless an environment switch asks for a particular loop or
 // kernel, up to one row per thread of one workgroup per CU.
 bool resident_wanted(spk_ctx ctx, const spk_solver_cfg &cfg, int64_t n) {
