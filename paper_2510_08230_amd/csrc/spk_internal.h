@@ -106,11 +106,11 @@ struct ResidentSolve {
     void *xch;                // exchange buffers (resident_exchange_bytes), zero before the first launch
     double *xd;
     double *x0;               // x as it was, for the loop that follows a time-out
-    ResidentState *state;     // the plan's block: the state, the control words, the words of the sums
-    unsigned *ctl;
     unsigned long long *slots;
+    unsigned *ctl;
     unsigned epoch;           // 1, 2, ... per launch on this block
     unsigned long long gate_ticks, spin_ticks;   // wall-clock limits of the start and of one wait
+    ResidentState *state;     // the plan's block: the state, the control words, the words of the sums
     double tau, tau_in;
     int64_t max_iters, max_outer;
     double *hist;

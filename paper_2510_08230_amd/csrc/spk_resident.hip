@@ -200,7 +200,6 @@ struct GridSum {
         const int G = gridDim.x, tid = threadIdx.x, lane = tid & 63;
         const int g = blockIdx.x, group = g / kGroup, member = g % kGroup, groups = (G + kGroup - 1) / kGroup;
         const int rows = blockDim.x >> 4, j = lane / kGroup, i = lane % kGroup;
-        const int gone = *late;   // read here, ahead of the barrier: its latency is hidden
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
             const double t = row_total(v[u]);
@@ -222,7 +221,7 @@ struct GridSum {
         }
         bool there = gather();   // the words of workgroups that are ahead are there already
         if (tid < 64) {
-            int bad = gone;
+            int bad = *late;   // set before the barrier of this sum, if at all
             const bool one = groups == 1;   // its members' slots are read directly
             if (member == 0 && !one) {
                 const double t = collect(set(syncs, kCopies + group), lane, j < NV && group * kGroup + i < G, bad);
@@ -239,7 +238,7 @@ struct GridSum {
             there = gather();
             if (spins > kMaxSpins) {
                 fail();
-                *late = 1;   // the workgroup leaves at one of the next sums
+                *late = 1;   // the workgroup leaves at the next sum
                 break;
             }
         }
