@@ -279,7 +279,7 @@ __device__ __forceinline__ bool rendezvous(unsigned *ctl, unsigned epoch, unsign
 // refinement's matrix.
 template <typename T, typename V, typename V64>
 __global__ __launch_bounds__(kResidentRows) void k_resident(ResidentSolve a) {
-    extern __shared__ char smem[];
+    extern __shared__ __attribute__((aligned(8))) char smem[];   // doubles first
     __shared__ int s_late;
     if (threadIdx.x == 0) s_late = 0;
     if (!rendezvous(a.ctl, a.epoch, a.gate_ticks)) return;
